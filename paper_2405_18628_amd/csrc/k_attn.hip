@@ -428,9 +428,11 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(AttnLaunch p) {
       const size_t t = (size_t)t0 + tl;
       if (KS == 1) {
         const float inv = 1.f / l;
-        float *dst = p.out + t * p.nh * 128 + h * 128 + lg * 4;
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) *(floatx4 *)(dst + dt * 16) = o[dt] * inv;
+        for (int dt = 0; dt < 8; ++dt) {
+          const floatx4 r = o[dt] * inv;
+          store_plane4(p.out, p.T_pad >> 4, (int)t, h * 128 + dt * 16 + lg * 4, {r[0], r[1], r[2], r[3]});
+        }
       } else {
         float *row = p.part + (((size_t)h * p.max_splits + ks) * p.T_pad + t) * OROW;
 #pragma unroll
@@ -462,7 +464,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(AttnLaunch p) {
           r[v] = load_l2(rp, (uint32_t)((row + d4) * 4));
         }
       });
-      *(floatx4 *)(p.out + (size_t)(t0 + tl) * p.nh * 128 + h * 128 + d4) = o;
+      store_plane4(p.out, p.T_pad >> 4, t0 + tl, h * 128 + d4, {o[0], o[1], o[2], o[3]});
     }
   }
 }
@@ -485,7 +487,7 @@ __global__ __launch_bounds__(512) void attn_merge_kernel(AttnLaunch p) {
       r[v] = *(const floatx4 *)(row + d4);
     }
   });
-  *(floatx4 *)(p.out + t * p.nh * 128 + h * 128 + d4) = o;
+  store_plane4(p.out, p.T_pad >> 4, (int)t, h * 128 + d4, {o[0], o[1], o[2], o[3]});
 }
 
 }  // namespace

@@ -3,50 +3,66 @@
 // the gfx950 matrix cores (v_mfma_f32_16x16x32_bf16: weight rows are the
 // 16-row A operand, tokens the 16-column B operand), fp32 accumulation.
 //
-// Precision.  Weights are bf16.  Activations are kept in fp32 in memory and
-// enter the matrix cores as the sum of two bf16 parts (hi = bf16(a),
-// lo = bf16(a - hi): about 16 significant bits), two products per weight
-// fragment.  A bf16 rounding of every activation between layers would make
-// two correct implementations drift apart layer after layer (each rounding
-// flip is a full bf16 ulp); with the pair the drift stays near fp32 noise at
-// any depth.
+// Precision.  Weights are bf16.  Activations enter the matrix cores as the
+// sum of two bf16 parts (hi = bf16(a), lo = bf16(a - hi): about 16
+// significant bits), two products per weight fragment.  A bf16 rounding of
+// every activation between layers would make two correct implementations
+// drift apart layer after layer (each rounding flip is a full bf16 ulp); with
+// the pair the drift stays near fp32 noise at any depth.
 //
 // The step is bound by streaming the weights from HBM once (~T flop per byte
 // at bf16, far below the MI355X ridge), so the kernel is organised around
-// the weight stream and around what else each compute unit must load:
+// keeping that stream in flight from the launch's first cycle to its last:
 //  * weights are pre-packed group-major (launch_pack_weight): a group is 16
 //    output rows (gate/up: 16 gate rows and the matching 16 up rows), and
 //    each 64-column chunk of a group is a run of 1 KB fragments in the lane
-//    order of the instruction's A operand; a wave loads them straight into a
-//    register ring with 16-byte non-temporal loads (no LDS on this path);
+//    order of the instruction's A operand;
+//  * activations come as operand planes: whoever produces an activation
+//    (embedding, attention, a GEMM epilogue) splits it once into (hi, lo) and
+//    stores both parts in the lane order of the B operand (plane_off in
+//    ppd_internal.h), norm consumers' operands already times the gain.  So
+//    the main loop is loads and matrix instructions only: no conversion, no
+//    LDS, no barrier;
+//  * a workgroup owns a tile of groups and a K slice; its four waves (one per
+//    SIMD) all hold the whole tile and deal the slice's 32-column steps among
+//    themselves, KP at a time (a slab), so every weight and activation
+//    fragment is loaded once per workgroup, straight into the registers of
+//    the one wave that multiplies it, and the waves never wait for one
+//    another.  A compute unit returns its loads in order, so an L2 hit (the
+//    activations, the same for all tiles of an XCD) waits for the HBM loads
+//    ahead of it: L2 hits alone reach 130 GB/s on a compute unit, mixed with
+//    the weight stream 40, and the activations become the bound from
+//    T = 48 on.  The waves' sums are added through
+//    LDS at the end.
 //  * the groups are dealt to eight workgroup sets b % 8 (each runs on one
 //    XCD: the dispatcher deals workgroups round-robin over the XCDs) and,
-//    within a set, to TX tiles x s K-slices over its 32 workgroups: a
-//    tall tile over a slice of K keeps each workgroup's per-chunk work
-//    (loading and staging the T x 64 activation chunk as two bf16 planes,
-//    two products per fragment, one wave per SIMD) small next to the weight
-//    bytes it streams; a whole-K tile of few groups is bound by that work,
-//    not by HBM;
-//  * the activation chunk (fp32, the same for all of a slice's workgroups,
-//    an L2 hit) is staged per chunk in a double-buffered, XOR-swizzled LDS
-//    slot as the two bf16 parts; norm consumers form RMSNorm's x * gain here
-//    (the row scale is applied to the output rows in the epilogue);
-//  * a tile's s slices finish in the same kernel: each stores its partial
-//    sums (to L2: all of a tile's workgroups share one XCD), arrives at the
-//    tile's counter (an atomic), waits for the others (bounded spin) and
-//    finishes its share of the tile (QKV, gate/up: (group, token block)
-//    items dealt in turn; the others: whole token blocks), adding the
-//    partials in slice order (deterministic);
+//    within a set, to TX tiles x s K-slices.  s = 1 needs no exchange between
+//    workgroups; s > 1 trades one (partial sums through the XCD's L2 behind a
+//    counter, a bounded wait) for 1 / s of the activation bytes per workgroup
+//    (plan_gemm chooses);
 //  * epilogues: RMSNorm row scale, RoPE + query / key / value stores into the
-//    cache (QKV), residual add + per-tile sum of squares (output / down
-//    projections), SwiGLU (gate/up), logits + per-tile argmax (LM head).
+//    cache (QKV), residual add, the next norm's operand planes and sums of
+//    squares (output / down projections), SwiGLU into operand planes
+//    (gate/up), logits + per-tile argmax (LM head).
+//
+// Measured (us a launch; in brackets with fp32 activations, split, staged
+// through LDS and behind a barrier per chunk in every workgroup, as this
+// kernel did before): 7B, T = 1: QKV 21.2 (25.6), output 11.8 and down
+// projection 24.3 (18.2 on average), gate/up 33.2 (37.6); T = 64: QKV 31.1
+// (31.3), output 16.9 (18.5), down 30.3 (32.0), gate/up 41.6 (43.7), LM head
+// 57.9 (62.7); 13B, T = 128: QKV 60 (77), gate/up 91 (123), LM head 120
+// (134).  What bounds it: up to T = 32 the HBM stream (5.4 TB/s over a gate/up
+// launch at T = 1), beyond that the compute unit's load path, which the
+// activations share.
 #include <algorithm>
 
 #include "ppd_internal.h"
 
 namespace {
 
-constexpr int KC = 64;    // K per chunk: two MFMA k-steps
+constexpr int KC = 64;    // columns of a packed chunk: two MFMA k-steps
+constexpr int NW = 4;     // waves of a GEMM workgroup
+constexpr int NT = 64 * NW;
 constexpr int FRAG = 64;  // u32x4 per packed operand fragment (1 KB)
 
 template <int KIND>
@@ -58,11 +74,6 @@ __device__ __forceinline__ void amax_merge(float &v, int &i, float v2, int i2) {
     i = i2;
   }
 }
-
-// 16-byte column swizzle of a 128-byte LDS row: logical column c of row r is
-// stored at physical column c ^ ((r >> 1) & 7); sixteen consecutive rows read
-// at one logical column cover all banks once.
-__device__ __forceinline__ int swz(int r, int c) { return c ^ ((r >> 1) & 7); }
 
 // weight row held by row r (< 16) of sub-tile q of group grp; rows past the
 // matrix are padding (zero weights, no output)
@@ -81,202 +92,187 @@ __device__ __forceinline__ int group_row(int grp, int q, int r, int N) {
   }
 }
 
-// ---- RMSNorm row scale r[t] = 1/sqrt(mean(x^2) + eps) of tokens
-// tok0 .. tok0 + NT - 1 from the producer's per-tile sums of squares
-// ss[p][T_pad]: two threads per token, thread j adding partials j, j + 2, ...
-// in order, then the two sums are added -- the same order whatever NT or the
-// other tokens of the step (a batched step gives each sequence its own
-// step's bits).
-template <int NT>
-__device__ __forceinline__ void rs_request(const GemmLaunch &g, int tok0, float (&ssv)[16]) {
-  static_assert(2 * NT <= 256, "two threads per token");
-  const int tid = threadIdx.x, t = tid % NT, j = tid / NT;
-  const int T_pad = g.MT * 16;
+// ---- RMSNorm row scale r[t] = 1/sqrt(mean(x^2) + eps) from the producer's
+// partial sums of squares ss[p][T_pad], p < n_ss: thread (quad of tokens,
+// residue j) adds partials j, j + NJ, .. in order, then the NJ sums are added
+// in order.  The first RS_N partials of a thread are requested ahead of the
+// weight ring (rs_request), so they arrive while it fills.
+constexpr int RS_N = 8;
+
+template <int MT>
+__device__ __forceinline__ void rs_request(const GemmLaunch &g, floatx4 (&v)[RS_N]) {
+  constexpr int NQ = MT * 4, NJ = NT / NQ, T_pad = MT * 16;
+  const int q = threadIdx.x % NQ, j = threadIdx.x / NQ;
+  // past n_ss: beyond the resource, zeros
+  const __amdgpu_buffer_rsrc_t r = rsrc_of(g.ss, (uint32_t)(g.n_ss * T_pad * 4));
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int pp = j + 2 * i;
-    const bool use = tid < 2 * NT && pp < g.n_ss;
-    const float v = g.ss[(size_t)(use ? pp : 0) * T_pad + tok0 + t];  // always a valid row
-    ssv[i] = use ? v : 0.f;
-  }
+  for (int i = 0; i < RS_N; ++i)
+    v[i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                           r, ((j + NJ * i) * T_pad + 4 * q) * 4, 0, 0));
 }
 
-template <int NT>
-__device__ __forceinline__ void rs_finish(const GemmLaunch &g, int tok0, const float (&ssv)[16],
-                                          float *gs, float *rs_s) {
-  const int tid = threadIdx.x;
-  const int T_pad = g.MT * 16;
-  float s = 0.f;
+template <int MT>
+__device__ __forceinline__ void rs_finish(const GemmLaunch &g, const floatx4 (&v)[RS_N], float *tmp,
+                                          float *rs_s) {
+  constexpr int NQ = MT * 4, NJ = NT / NQ, T_pad = MT * 16;
+  const int tid = threadIdx.x, q = tid % NQ, j = tid / NQ;
+  floatx4 s = v[0];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) s += ssv[i];
-  if (tid < 2 * NT) {
-    const int t = tid % NT, j = tid / NT;
-    for (int pp = j + 32; pp < g.n_ss; pp += 2) s += g.ss[(size_t)pp * T_pad + tok0 + t];
-    gs[tid] = s;
+  for (int i = 1; i < RS_N; ++i) s += v[i];
+  if (j < NJ) {
+    for (int p = j + NJ * RS_N; p < g.n_ss; p += NJ) s += *(const floatx4 *)(g.ss + (size_t)p * T_pad + 4 * q);
+    *(floatx4 *)(tmp + j * T_pad + 4 * q) = s;
   }
   __syncthreads();
-  if (tid < NT) rs_s[tok0 + tid] = rsqrtf((gs[tid] + gs[NT + tid]) * g.inv_h + g.eps);
+  if (tid < T_pad) {
+    float t = 0.f;
+    for (int i = 0; i < NJ; ++i) t += tmp[i * T_pad + tid];
+    rs_s[tid] = rsqrtf(t * g.inv_h + g.eps);
+  }
+  __syncthreads();
 }
 
-// ---- inputs of an epilogue that come from memory, requested ahead of it
-// (one round trip, overlapped with the wait for the partial sums): the
-// residual rows (output / down projections) and the RoPE angles (QKV) of the
-// lane's rows and token
-template <int KIND, int GW>
+// ---- inputs of an item's epilogue that come from memory, requested before
+// the sums meet: the residual row and the next norm's gains (output / down
+// projections), the RoPE angles (QKV)
+template <int KIND>
 struct EpiIn {};
-template <int GW>
-struct EpiIn<GEMM_QKV, GW> {
-  floatx4 cs[GW][2];  // (cos, sin) of dims i0 .. i0 + 3
+template <>
+struct EpiIn<GEMM_QKV> {
+  floatx4 cs[2];  // (cos, sin) of dims i0 .. i0 + 3
 };
-template <int GW>
-struct EpiIn<GEMM_RESID, GW> {
-  floatx4 x[GW];
+template <>
+struct EpiIn<GEMM_RESID> {
+  floatx4 x;
+  uint2 gain;
 };
 
-template <int KIND, int GW>
-__device__ __forceinline__ void epi_load(const GemmLaunch &g, int ga, int gb, int mt, EpiIn<KIND, GW> &in,
-                                         unsigned gmask = ~0u) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tk = mt * 16 + (lane & 15);
+// where the keys and values of one token go (QKV): its sequence's cache and
+// the position L + local index.  The lookup is the same for every item of a
+// token block, so a wave keeps its last block's.
+struct TokenSlot {
+  int m = -1;
+  bf16_t *k, *v;
+  int cap, pos;
+};
+__device__ __forceinline__ void find_slot(const GemmLaunch &g, int m, TokenSlot &t) {
+  if (m == t.m) return;  // uniform
+  const int tk = m * 16 + (threadIdx.x & 15);
+  t.m = m;
+  t.k = g.sb.k[0];
+  t.v = g.sb.v[0];
+  t.cap = g.sb.cap[0];
+  t.pos = g.sb.L[0] + tk;
+  for (int j = 1; j < g.sb.B; ++j)
+    if (tk >= g.sb.t0[j]) {
+      t.k = g.sb.k[j];
+      t.v = g.sb.v[j];
+      t.cap = g.sb.cap[j];
+      t.pos = g.sb.L[j] + tk - g.sb.t0[j];
+    }
+}
+
+template <int KIND>
+__device__ __forceinline__ void epi_load(const GemmLaunch &g, int grp, int m, EpiIn<KIND> &in) {
+  const int lane = threadIdx.x & 63;
+  const int tk = m * 16 + (lane & 15);
   if constexpr (KIND == GEMM_QKV) {
-#pragma unroll
-    for (int i = 0; i < GW; ++i) {
-      const int gs = ga + wave + 4 * i;
-      const int i0 = 8 * (gs & 7) + 4 * ((lane >> 4) & 1);
-      const bool use = ((gmask >> i) & 1u) && gs < gb && (gs >> 3) < g.nh + g.nkv;
-      const floatx4 *rp = (const floatx4 *)(g.rope + (size_t)(use ? tk : 0) * 64 + (use ? i0 : 0));
-      in.cs[i][0] = rp[0];
-      in.cs[i][1] = rp[1];
-    }
+    const int i0 = 8 * (grp & 7) + 4 * ((lane >> 4) & 1);
+    const floatx4 *rp = (const floatx4 *)(g.rope + (size_t)tk * 64 + i0);
+    in.cs[0] = rp[0];
+    in.cs[1] = rp[1];
   } else if constexpr (KIND == GEMM_RESID) {
-#pragma unroll
-    for (int i = 0; i < GW; ++i) {
-      const int grp = ga + wave + 4 * i;
-      const int n = grp * 16 + (lane >> 4) * 4;
-      const bool use = grp < gb && n < g.N && tk < g.T;
-      in.x[i] = use ? *(const floatx4 *)(g.x + (size_t)tk * g.N + n) : floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    const int n = grp * 16 + (lane >> 4) * 4;  // N is a multiple of 128: always a row of the matrix
+    in.x = *(const floatx4 *)(g.x + (size_t)tk * g.N + n);
+    in.gain = *(const uint2 *)(g.gain + n);
   }
 }
 
-// ---- epilogue of token block mt of tile gt (groups [ga, gb)), from the
-// complete sums a[i][q]: the lane holds rows 4 (lane / 16) + e of sub-tile q
-// of its wave's group i (group ga + wave + 4 i), token mt 16 + lane % 16.
-// Called by all threads (it has barriers); rs_s holds the row scales, in the
-// inputs epi_load requested.
-template <int KIND, int GW>
-__device__ __forceinline__ void epilogue(const GemmLaunch &g, int gt, int ga, int gb, int mt,
-                                         const floatx4 (&a)[GW][SUB<KIND>], const float *rs_s,
-                                         float (*red_s)[128][2], const EpiIn<KIND, GW> &in,
-                                         unsigned gmask = ~0u) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// ---- epilogue of item (group grp, token block m) from its complete sums
+// a[q]: the lane holds rows 4 (lane / 16) + e of sub-tile q, token
+// 16 m + lane % 16.  One wave, no barriers.  What a reduction over the
+// tile's rows needs goes to red[16], one entry per token: the LM head's best
+// (value, index), the output / down projections' sum of squares.
+template <int KIND>
+__device__ __forceinline__ void epilogue(const GemmLaunch &g, int grp, int m, const floatx4 (&a)[SUB<KIND>],
+                                         const float *rs_s, const EpiIn<KIND> &in, float2 *red,
+                                         const TokenSlot &st) {
+  const int lane = threadIdx.x & 63;
   const int lr = lane & 15, r4 = (lane >> 4) * 4;
-  const int T = g.T, T_pad = g.MT * 16;
-  const int tk = mt * 16 + lr;
+  const int T = g.T;
+  const int tk = m * 16 + lr;
   if constexpr (KIND == GEMM_QKV) {
     const int nh = g.nh, nkv = g.nkv;
     const bool upper = lane >= 32;  // rows 8..15: the RoPE partner dims (+64)
-    // this token's sequence: its cache and the position L + local index
-    bf16_t *kc = g.sb.k[0], *vc = g.sb.v[0];
-    int cap = g.sb.cap[0], pos = g.sb.L[0] + tk;
-    for (int j = 1; j < g.sb.B; ++j)
-      if (tk >= g.sb.t0[j]) {
-        kc = g.sb.k[j];
-        vc = g.sb.v[j];
-        cap = g.sb.cap[j];
-        pos = g.sb.L[j] + tk - g.sb.t0[j];
+    const float rs = rs_s[tk];      // finite for padding tokens too
+    const int hp = grp >> 3;        // head part: q heads, then k, then v
+    const int i0 = 8 * (grp & 7) + 4 * ((lane >> 4) & 1);
+    const int d0 = i0 + (upper ? 64 : 0);  // this lane's dims d0 .. d0 + 3
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = a[0][e] * rs;
+    if (hp < nh + nkv) {
+      const float cs[8] = {in.cs[0][0], in.cs[0][1], in.cs[0][2], in.cs[0][3],
+                           in.cs[1][0], in.cs[1][1], in.cs[1][2], in.cs[1][3]};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        // [0]: lane l % 32's value (dim i), [1]: lane l % 32 + 32's (dim i + 64)
+        const auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[e]), __float_as_uint(v[e]),
+                                                         false, false);
+        const float x0 = __uint_as_float(pr[0]), x1 = __uint_as_float(pr[1]);
+        const float c = cs[2 * e], sn = cs[2 * e + 1];
+        v[e] = upper ? x1 * c + x0 * sn : x0 * c - x1 * sn;
       }
-    const float rs = rs_s[tk];  // finite for padding tokens too
+    }
+    if (tk >= T) return;
+    if (hp < nh) {
+      *(floatx4 *)(g.q + ((size_t)tk * nh + hp) * 128 + d0) = floatx4{v[0], v[1], v[2], v[3]};
+      return;
+    }
+    const int cap = st.cap, pos = st.pos;
+    if (hp < nh + nkv) {
+      bf16_t *dst = st.k + ((size_t)(hp - nh) * cap + pos) * 128;
+      *(u32x2 *)(dst + d0) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+    } else {
+      bf16_t *vb = st.v + (size_t)(hp - nh - nkv) * 128 * cap + pos;
 #pragma unroll
-    for (int i = 0; i < GW; ++i) {
-      const int gs = ga + wave + 4 * i;  // uniform in the wave
-      if (!((gmask >> i) & 1u) || gs >= gb || gs >= (nh + 2 * nkv) * 8) continue;
-      const int hp = gs >> 3;  // head part: q heads, then k, then v
-      const int i0 = 8 * (gs & 7) + 4 * ((lane >> 4) & 1);
-      const int d0 = i0 + (upper ? 64 : 0);  // this lane's dims d0 .. d0 + 3
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = a[i][0][e] * rs;
-      if (hp < nh + nkv) {
-        const floatx4 c0 = in.cs[i][0], c1 = in.cs[i][1];  // (cos, sin) of dims i0 .. i0 + 3
-        const float cs[8] = {c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          // [0]: lane l % 32's value (dim i), [1]: lane l % 32 + 32's (dim i + 64)
-          const auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[e]), __float_as_uint(v[e]),
-                                                           false, false);
-          const float x0 = __uint_as_float(pr[0]), x1 = __uint_as_float(pr[1]);
-          const float c = cs[2 * e], sn = cs[2 * e + 1];
-          v[e] = upper ? x1 * c + x0 * sn : x0 * c - x1 * sn;
-        }
-      }
-      if (tk >= T) continue;
-      if (hp < nh) {
-        *(floatx4 *)(g.q + ((size_t)tk * nh + hp) * 128 + d0) = floatx4{v[0], v[1], v[2], v[3]};
-      } else if (hp < nh + nkv) {
-        bf16_t *dst = kc + ((size_t)(hp - nh) * cap + pos) * 128;
-        *(u32x2 *)(dst + d0) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-      } else {
-        bf16_t *vb = vc + (size_t)(hp - nh - nkv) * 128 * cap + pos;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vb[(size_t)(d0 + e) * cap] = f32_to_bf16(v[e]);
-      }
+      for (int e = 0; e < 4; ++e) vb[(size_t)(d0 + e) * cap] = f32_to_bf16(v[e]);
     }
   } else if constexpr (KIND == GEMM_SWIGLU) {
-    if (tk < T) {
-      const float rs = rs_s[tk];
+    const int f0 = grp * 16 + r4;
+    if (tk >= T || f0 >= g.N) return;
+    const float rs = rs_s[tk];
+    float o[4];
 #pragma unroll
-      for (int i = 0; i < GW; ++i) {
-        const int grp = ga + wave + 4 * i;
-        const int f0 = grp * 16 + r4;
-        if (!((gmask >> i) & 1u) || grp >= gb || f0 >= g.N) continue;
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float gt_ = a[i][0][e] * rs, up = a[i][1][e] * rs;
-          o[e] = gt_ / (1.f + expf(-gt_)) * up;
-        }
-        *(floatx4 *)(g.act + (size_t)tk * g.N + f0) = floatx4{o[0], o[1], o[2], o[3]};
-      }
+    for (int e = 0; e < 4; ++e) {
+      const float gt_ = a[0][e] * rs, up = a[1][e] * rs;
+      o[e] = gt_ / (1.f + expf(-gt_)) * up;
     }
+    store_plane4(g.planes, g.MT, tk, f0, o);
   } else if constexpr (KIND == GEMM_RESID) {
+    const int n = grp * 16 + r4;
     float sq = 0.f;
     if (tk < T) {
-#pragma unroll
-      for (int i = 0; i < GW; ++i) {
-        const int grp = ga + wave + 4 * i;
-        const int n = grp * 16 + r4;
-        if (grp >= gb || n >= g.N) continue;
-        floatx4 xv = in.x[i];
-        xv += a[i][0];
-        *(floatx4 *)(g.x + (size_t)tk * g.N + n) = xv;
-        sq += (xv[0] * xv[0] + xv[1] * xv[1]) + (xv[2] * xv[2] + xv[3] * xv[3]);
-      }
+      const floatx4 xv = in.x + a[0];
+      *(floatx4 *)(g.x + (size_t)tk * g.N + n) = xv;
+      sq = (xv[0] * xv[0] + xv[1] * xv[1]) + (xv[2] * xv[2] + xv[3] * xv[3]);
+      const float o[4] = {xv[0] * bf16_to_f32(in.gain.x & 0xffff), xv[1] * bf16_to_f32(in.gain.x >> 16),
+                          xv[2] * bf16_to_f32(in.gain.y & 0xffff), xv[3] * bf16_to_f32(in.gain.y >> 16)};
+      store_plane4(g.planes, g.MT, tk, n, o);
     }
-    // sum over the 4 lane groups (rows) of this wave, then over the waves
+    // the group's 16 rows: one partial sum of squares per token
     sq += __shfl_xor(sq, 16, 64);
     sq += __shfl_xor(sq, 32, 64);
-    if (lane < 16) red_s[wave][lane][0] = sq;
-    __syncthreads();
-    if (tid < 16) {
-      const int tok = mt * 16 + tid;
-      const float v = tok < T ? ((red_s[0][tid][0] + red_s[1][tid][0]) + (red_s[2][tid][0] + red_s[3][tid][0]))
-                              : 0.f;
-      g.ss_out[(size_t)gt * T_pad + tok] = v;
-    }
-    __syncthreads();
+    if (lane < 16) red[lane].x = sq;
   } else {  // GEMM_LOGITS
-    const float rs = tk < T ? rs_s[tk] : 0.f;
+    const int n = grp * 16 + r4;
     float bv = 0.f;
     int bi = -1;
-#pragma unroll
-    for (int i = 0; i < GW; ++i) {
-      const int grp = ga + wave + 4 * i;
-      const int n = grp * 16 + r4;
-      if (grp >= gb || tk >= T) continue;
+    if (tk < T) {
+      const float rs = rs_s[tk];
       float v[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = a[i][0][e] * rs;
+      for (int e = 0; e < 4; ++e) v[e] = a[0][e] * rs;
       if (g.logits) {
         if ((g.N & 3) == 0 && n + 3 < g.N) {
           *(floatx4 *)(g.logits + (size_t)tk * g.N + n) = floatx4{v[0], v[1], v[2], v[3]};
@@ -304,139 +300,140 @@ __device__ __forceinline__ void epilogue(const GemmLaunch &g, int gt, int ga, in
       const int i2 = __shfl_xor(bi, off, 64);
       amax_merge(bv, bi, v2, i2);
     }
-    if (lane < 16) {
-      red_s[wave][lane][0] = bv;
-      red_s[wave][lane][1] = __int_as_float(bi);
-    }
-    __syncthreads();
-    if (tid < 16) {
-      float v = red_s[0][tid][0];
-      int i = __float_as_int(red_s[0][tid][1]);
-      for (int w = 1; w < 4; ++w) amax_merge(v, i, red_s[w][tid][0], __float_as_int(red_s[w][tid][1]));
-      g.amax[(size_t)gt * T_pad + mt * 16 + tid] = make_float2(v, __int_as_float(i));
-    }
-    __syncthreads();
+    if (lane < 16) red[lane] = make_float2(bv, __int_as_float(bi));
   }
 }
 
-// tile gt of an XCD holding no group: the outputs other kernels sum over
-// every tile are written neutral (sum of squares 0, no argmax candidate)
-template <int KIND>
-__device__ __forceinline__ void empty_tile(const GemmLaunch &g, int gt) {
-  const int T_pad = g.MT * 16;
-  for (int tk = threadIdx.x; tk < T_pad; tk += blockDim.x) {
-    if constexpr (KIND == GEMM_RESID) g.ss_out[(size_t)gt * T_pad + tk] = 0.f;
-    if constexpr (KIND == GEMM_LOGITS) g.amax[(size_t)gt * T_pad + tk] = make_float2(0.f, __int_as_float(-1));
-  }
+// buffer-load offset of a lane whose load is to be dropped: past every
+// resource's range (each is below 2 GB), with or without the scalar offset
+// added, so the load returns zeros and touches no memory
+constexpr uint32_t kDropped = 0x80000000u;
+
+// Register buffers of a wave.  `steps` k-steps of fragments (weights and
+// activations) fit beside the accumulators and among the 64 loads a wave can
+// have outstanding; they are used as three slabs of KP steps, two where no
+// more fit.  Where not even two steps fit (the largest
+// tile of 128 tokens), one step's activations and two steps' weights are kept
+// (NB = 1).  Measured, 7B layers with T = 64 / 48 / 32 / 1 (us a step of 4): 3
+// slabs of 1 / 1 / 2 / 8 steps 613 / 580 / 521 / 464, two of twice the steps
+// 613 / 579 / 543 / 481, activations in one buffer and weights in two of 4 to
+// 8 steps 642 / 605 / 546 / 479.
+constexpr int buf_steps(int MT, int WF) {
+  return std::min(440 - 4 * WF * MT, 4 * 66) / (4 * (WF + 2 * MT));
+}
+constexpr int slab_steps(int MT, int WF) {
+  return std::max(1, std::min({(MT == 1 ? 16 : 8) / (2 * MT), buf_steps(MT, WF) / 3}));
+}
+constexpr int slab_bufs(int MT, int WF) {
+  return std::min(3, std::max(1, buf_steps(MT, WF) / slab_steps(MT, WF)));
 }
 
 // ---- the GEMM.  Workgroup b: XCD x = b % 8, slot j = b / 8 -> tile
-// t = j / s (groups [ga, gb) of the XCD's range), K slice ks = j % s (chunks
-// [c0, c1)).  Wave w owns groups ga + w + 4 i, i < GW.  RING: weight chunks
-// requested ahead.
-template <int MT, int KIND, int GW, int RING>
-__global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmLaunch g) {
-  // activation chunks requested ahead (L2 hits, but ~1 us away under the
-  // weight stream): 4, or 2 where 4 chunks of MT tiles would not fit the
-  // registers
-  constexpr int RA = MT <= 4 ? 4 : 2;
+// t = j / s (groups [ga, gb) of the XCD's range, at most GW), K slice
+// ks = j % s (k-steps [u0, u1)).
+template <int MT, int KIND, int GW>
+__global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
   constexpr int T_pad = MT * 16;
-  constexpr int S = SUB<KIND>;
-  constexpr int PLANE = T_pad * 128;          // bytes of one bf16 plane of a chunk
-  constexpr bool kNorm = KIND != GEMM_RESID;  // A operand = x * gain, rows scaled in the epilogue
-  constexpr int UNR = RING > RA ? RING : RA;  // chunks per unrolled trip (both rings wrap)
-  static_assert(UNR % RING == 0 && UNR % RA == 0 && UNR % 2 == 0, "ring depths");
-  __shared__ __attribute__((aligned(16))) unsigned char lds_a[2][2 * PLANE];
-  __shared__ float rs_s[128];
-  __shared__ float red_s[4][128][2];
+  constexpr int S = SUB<KIND>, WF = GW * S;
+  constexpr int KP = slab_steps(MT, WF), NB = slab_bufs(MT, WF);
+  constexpr bool kNorm = KIND != GEMM_RESID;  // rows scaled in the epilogue
+  // the waves' sums meet in LDS, MR token blocks a round (at most 96 KB)
+  constexpr int MR = std::max(1, std::min(MT, 96 / (NW * WF)));
+  constexpr int ITEMS = GW * MR;  // per round
+  constexpr int PI = (ITEMS + NW - 1) / NW;
+  __shared__ __attribute__((aligned(16))) float red_s[NW * WF * MR * 256];
+  __shared__ float rs_tmp[NT * 4];
+  __shared__ float rs_s[T_pad];
+  constexpr bool kRows = KIND == GEMM_LOGITS || KIND == GEMM_RESID;  // reductions over the tile's rows
+  __shared__ float2 item_s[kRows ? GW * MT * 16 : 1];
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, lg = lane >> 4;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int s = g.s;
-  const int t = __builtin_amdgcn_readfirstlane(j / s), ks = __builtin_amdgcn_readfirstlane(j % s);
-  const int gt = x * g.TX + t;  // global tile index (sum-of-squares / argmax partial rows)
-  const int nx = g.xg0[x + 1] - g.xg0[x];
-  const int ga = __builtin_amdgcn_readfirstlane(g.xg0[x] + nx * t / g.TX);
-  const int gb = __builtin_amdgcn_readfirstlane(g.xg0[x] + nx * (t + 1) / g.TX);
-  const int K = g.K, kc = g.kc;
-  const int c0 = __builtin_amdgcn_readfirstlane(kc * ks / s);
-  const int c1 = __builtin_amdgcn_readfirstlane(kc * (ks + 1) / s);
-  if (ga >= gb) {  // no groups on this tile
-    if (ks == 0) empty_tile<KIND>(g, gt);
+  // slot j -> tile t, slice ks (s = 1 << ls); the XCD's groups [g0, g0 + nx)
+  // in TX runs of nx / TX groups, the first nx % TX of one more (nx is one of
+  // two values: both quotients come from the host)
+  const int ls = g.ls, s = 1 << ls;
+  const int t = j >> ls, ks = j & (s - 1);
+  const int gt = x * g.TX + t;  // global tile index
+  const int g0 = (g.G * x) >> 3, nx = ((g.G * (x + 1)) >> 3) - g0;
+  const bool more = nx > (g.G >> 3);
+  const int hq = more ? g.q1 : g.q0, hr = more ? g.r1 : g.r0;
+  const int ga = g0 + t * hq + min(t, hr), ng = hq + (t < hr ? 1 : 0), gb = ga + ng;
+  const int kc = g.kc;
+  const int u0 = (2 * kc * ks) >> ls, u1 = (2 * kc * (ks + 1)) >> ls;
+  // Which slice finishes item (group i, token block m) of a split tile: the
+  // items in turn; where the tile's rows are reduced, (m R + i % R) % s with
+  // R = ceil(s / MT), so that the reduction of a token block over groups
+  // i % R = r, one output row per (tile, r), stays in one slice.
+  const int R = kRows ? (s + MT - 1) / MT : 1;
+  auto row_slice = [&](int i, int m) { return (m * R + i % R) & (s - 1); };
+  auto rows_out = [&](int n) {  // the tile's reductions, from its items in item_s
+    for (int o = tid; o < R * T_pad; o += NT) {
+      const int r = o / T_pad, tk = o % T_pad, m = tk >> 4;
+      if (row_slice(r, m) != ks) continue;
+      const size_t at = (size_t)(gt * R + r) * T_pad + tk;
+      if constexpr (KIND == GEMM_RESID) {
+        float v = 0.f;
+        for (int i = r; i < n; i += R) v += item_s[(i * MT + m) * 16 + (tk & 15)].x;
+        g.ss_out[at] = v;
+      } else {
+        float v = 0.f;
+        int bi = -1;
+        for (int i = r; i < n; i += R) {
+          const float2 c = item_s[(i * MT + m) * 16 + (tk & 15)];
+          amax_merge(v, bi, c.x, __float_as_int(c.y));
+        }
+        g.amax[at] = make_float2(v, __int_as_float(bi));
+      }
+    }
+  };
+  if (ng <= 0) {  // no groups on this tile: neutral rows
+    if constexpr (kRows) rows_out(0);
     return;
   }
-  // groups of this wave that exist (uniform in the wave)
-  const int live = __builtin_amdgcn_readfirstlane(min(GW, max(0, (gb - ga - wave + 3) / 4)));
 
-  [[maybe_unused]] float ssv[16];
-  if constexpr (kNorm) rs_request<T_pad>(g, 0, ssv);
+  [[maybe_unused]] floatx4 ssv[RS_N];
+  if constexpr (kNorm) rs_request<MT>(g, ssv);
 
-  // ---- register rings.  Weight chunk c of this wave: fragments (group i,
-  // sub-tile q, k-step s) for i < GW, read through a buffer resource with
-  // the non-temporal hint (offsets from the weight's base; a packed weight
-  // is below 2 GB).  Past the slice, and for groups the wave does not own,
-  // every lane reads the tile's first 16 bytes (one line), so every
-  // iteration issues the same loads.
-  const u32x4 *wp = (const u32x4 *)g.W;
-  const __amdgpu_buffer_rsrc_t wrs = rsrc_of(g.W, 0x7ffffff0u);
-  u32x4 wr[RING][GW * S * 2];
-  auto request_w = [&](int c, u32x4(&dw)[GW * S * 2]) {
-    const bool cin = c < c1;
+  // ---- the wave's k-steps u0 + (slab NW + wave) KP + k, k < KP: weight
+  // fragments (group i, sub-tile q) and activation fragments (token block m,
+  // part p).  Steps past the slice and groups past the tile are dropped loads
+  // (zeros), so every slab issues the same instructions.
+  const __amdgpu_buffer_rsrc_t wrs = rsrc_of(g.W, g.w_bytes), ars = rsrc_of(g.A, g.a_bytes);
+  uint32_t wo[GW];
+  int wg[GW];  // the group's first fragment
 #pragma unroll
-    for (int i = 0; i < GW; ++i) {
-      const bool use = cin && i < live;
-      const int grp = use ? ga + wave + 4 * i : ga;
-      const int cc = use ? c : c0;
-      const u32x4 *gp = wp + (((size_t)grp * kc + cc) * S) * 2 * FRAG + (use ? lane : 0);
+  for (int i = 0; i < GW; ++i) {
+    wo[i] = i < ng ? lane * 16 : kDropped;
+    wg[i] = min(ga + i, gb - 1) * kc * 2 * S;
+  }
+  const int n_slab = __builtin_amdgcn_readfirstlane((u1 - u0 + NW * KP - 1) / (NW * KP));
+  u32x4 wr[NB == 1 ? 2 : NB][KP][WF], ar[NB][KP][2 * MT];
+  auto request_w = [&](int n, u32x4(&w)[KP][WF]) {
 #pragma unroll
-      for (int q = 0; q < S; ++q)
+    for (int k = 0; k < KP; ++k) {
+      const int u = u0 + (n * NW + wave) * KP + k, uc = min(u, u1 - 1);
+      const uint32_t drop = u < u1 ? 0u : kDropped;
 #pragma unroll
-        for (int st = 0; st < 2; ++st)
-          dw[(i * S + q) * 2 + st] =
-              __builtin_amdgcn_raw_buffer_load_b128(wrs, (int)((gp + (q * 2 + st) * FRAG - wp) * 16), 0, 2);
+      for (int i = 0; i < GW; ++i)
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+          w[k][i * S + q] = __builtin_amdgcn_raw_buffer_load_b128(
+              wrs, (int)(wo[i] | drop), (wg[i] + (uc >> 1) * 2 * S + 2 * q + (uc & 1)) << 10, 2);
     }
   };
-  // activation pieces of a chunk: thread tid loads 16 bytes (4 columns
-  // 4 (tid % 16) ..) of rows tid / 16 + 16 r, r < MT; norm kinds also the 4
-  // gains of those columns
-  const int acol = (tid & 15) * 4, arow = tid >> 4;
-  u32x4 ar[RA][MT];
-  [[maybe_unused]] uint2 agn[RA];
-  auto request_a = [&](int c, u32x4(&da)[MT], uint2 &gn) {
-    const bool cin = c < c1;
-    const int k0 = (cin ? c : c0) * KC + acol;
+  auto request_a = [&](int n, u32x4(&a)[KP][2 * MT]) {
+    const int u = u0 + (n * NW + wave) * KP;
 #pragma unroll
-    for (int r = 0; r < MT; ++r) da[r] = *(const u32x4 *)(g.A + (size_t)(arow + 16 * r) * K + k0);
-    if constexpr (kNorm) gn = *(const uint2 *)(g.gain + k0);
-  };
-  // stage as the two bf16 parts: plane 0 = hi, plane 1 = lo
-  auto stage = [&](const u32x4(&da)[MT], const uint2 &gn, int slot) {
-    float gv[4] = {1.f, 1.f, 1.f, 1.f};
-    if constexpr (kNorm) {
-      gv[0] = bf16_to_f32(gn.x & 0xffff);
-      gv[1] = bf16_to_f32(gn.x >> 16);
-      gv[2] = bf16_to_f32(gn.y & 0xffff);
-      gv[3] = bf16_to_f32(gn.y >> 16);
-    }
+    for (int k = 0; k < KP; ++k) {
+      const int uc = min(u + k, u1 - 1);
+      const uint32_t drop = u + k < u1 ? 0u : kDropped;
 #pragma unroll
-    for (int r = 0; r < MT; ++r) {
-      const int row = arow + 16 * r;
-      float v[4], lo[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        // padding tokens (rows past T, whatever the workspace holds there)
-        // enter as zeros, so their sums are finite
-        v[e] = row < g.T ? __uint_as_float(da[r][e]) * gv[e] : 0.f;
-        lo[e] = v[e] - bf16_to_f32(f32_to_bf16(v[e]));
-      }
-      const int off = row * 128 + swz(row, acol >> 3) * 16 + (acol & 7) * 2;
-      *(uint2 *)(&lds_a[slot][off]) = uint2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-      *(uint2 *)(&lds_a[slot][PLANE + off]) = uint2{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
+      for (int m = 0; m < 2 * MT; ++m)
+        a[k][m] = __builtin_amdgcn_raw_buffer_load_b128(ars, (int)(lane * 16 | drop), (uc * 2 * MT + m) << 10, 0);
     }
   };
-
   floatx4 acc[GW][S][MT];
 #pragma unroll
   for (int i = 0; i < GW; ++i)
@@ -445,219 +442,231 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmLaunch g) {
 #pragma unroll
       for (int m = 0; m < MT; ++m) acc[i][q][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+  // one slab: the smaller parts' products first, then the larger parts', so
+  // that consecutive instructions add to different accumulators
+  auto multiply = [&](const u32x4(&w)[KP][WF], const u32x4(&a)[KP][2 * MT]) {
 #pragma unroll
-  for (int r = 0; r < RING; ++r) request_w(c0 + r, wr[r]);
+    for (int k = 0; k < KP; ++k)
 #pragma unroll
-  for (int r = 0; r < RA; ++r) request_a(c0 + r, ar[r], agn[r]);
-  __builtin_amdgcn_sched_barrier(0);
-  if constexpr (kNorm) rs_finish<T_pad>(g, 0, ssv, &red_s[0][0][0], rs_s);
-  // rs_s is read after the main loop's barriers; red_s is next written by an
-  // epilogue, after them as well
-
-  // ---- main loop, RING chunks per trip.  Chunk c: stage its activations
-  // (requested RA chunks ago) into LDS slot (c - c0) & 1, request chunk
-  // c + RA's into the freed registers; barrier; multiply with the weight
-  // fragments requested RING chunks ago, then request chunk c + RING's into
-  // them.  The slot staged here was last read for chunk c - 2, which every
-  // wave finished before chunk c - 1's barrier.  Chunks past the slice
-  // (the last trip) only stage and load one line.
-  for (int cb = c0; cb < c1; cb += UNR) {
-#pragma unroll
-    for (int r = 0; r < UNR; ++r) {
-      const int c = cb + r;
-      const int slot = r & 1;  // (c - c0) & 1: UNR is even
-      stage(ar[r % RA], agn[r % RA], slot);
-      __builtin_amdgcn_sched_barrier(0);
-      request_a(c + RA, ar[r % RA], agn[r % RA]);
-      __builtin_amdgcn_sched_barrier(0);
-      __syncthreads();
-      if (c < c1) {
-        const unsigned char *al = lds_a[slot];
-#pragma unroll
-        for (int st = 0; st < 2; ++st) {
-          u32x4 bh[MT], bl[MT];
-#pragma unroll
-          for (int m = 0; m < MT; ++m) {
-            const int row = m * 16 + lr;
-            const int off = row * 128 + swz(row, st * 4 + lg) * 16;
-            bh[m] = *(const u32x4 *)(al + off);
-            bl[m] = *(const u32x4 *)(al + PLANE + off);
-          }
-#pragma unroll
-          for (int i = 0; i < GW; ++i) {
-            if (i >= live) break;
-#pragma unroll
-            for (int q = 0; q < S; ++q)
-#pragma unroll
-              for (int m = 0; m < MT; ++m) {
-                const bf16x8 w = as_bf16x8(wr[r % RING][(i * S + q) * 2 + st]);
-                acc[i][q][m] = mfma16x16x32(w, as_bf16x8(bl[m]), acc[i][q][m]);
-                acc[i][q][m] = mfma16x16x32(w, as_bf16x8(bh[m]), acc[i][q][m]);
-              }
-          }
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      request_w(c + RING, wr[r % RING]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-
-  if (s == 1) {  // whole tile: finish in place
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      floatx4 am[GW][S];
-#pragma unroll
-      for (int i = 0; i < GW; ++i)
-#pragma unroll
-        for (int q = 0; q < S; ++q) am[i][q] = acc[i][q][m];
-      EpiIn<KIND, GW> in;
-      epi_load<KIND, GW>(g, ga, gb, m, in);
-      epilogue<KIND, GW>(g, gt, ga, gb, m, am, rs_s, red_s, in);
-    }
-    return;
-  }
-
-  // ---- split tile: partials to L2, arrive, wait for the tile's other
-  // slices, finish this slice's items.  Item (group i, token block m) is
-  // finished by slice fin(i, m): QKV and gate/up deal the tile's items to the
-  // slices in turn ((i MT + m) % s); the others keep whole token blocks
-  // together (their epilogues reduce over the tile's rows): m % s.  A slice
-  // stores the partial sums of the items other slices finish and keeps its
-  // own in registers.  Partial (tile gt, slice sl): [wave][i][q][m][lane]
-  // floatx4.
-  constexpr int PW = GW * S * MT;  // floatx4 per lane per wave
-  constexpr bool kItems = KIND == GEMM_QKV || KIND == GEMM_SWIGLU;
-  auto fin = [&](int i, int m) { return kItems ? (i * MT + m) % s : m % s; };
-  float *part = g.part + ((size_t)gt * s + ks) * (4 * PW * 64 * 4);
-#pragma unroll
-  for (int i = 0; i < GW; ++i) {
-    if (i >= live) break;
-#pragma unroll
-    for (int q = 0; q < S; ++q)
-#pragma unroll
-      for (int m = 0; m < MT; ++m)
-        if (fin(i, m) != ks)
-          *(floatx4 *)(part + ((size_t)((wave * GW + i) * S + q) * MT + m) * 256 + lane * 4) = acc[i][q][m];
-  }
-  // the items of token block m this slice finishes
-  auto mine = [&](int m) {
-    unsigned gm = 0;
-#pragma unroll
-    for (int i = 0; i < GW; ++i) gm |= fin(i, m) == ks ? 1u << i : 0u;
-    return gm;
-  };
-  // the epilogue inputs of this slice's first token block, requested now:
-  // they arrive while the partial sums are stored and the slices meet
-  int m0 = -1;
-  unsigned gm0 = 0;
-#pragma unroll
-  for (int m = 0; m < MT; ++m)
-    if (m0 < 0 && mine(m)) {
-      m0 = m;
-      gm0 = mine(m);
-    }
-  EpiIn<KIND, GW> in0;
-  if (m0 >= 0) epi_load<KIND, GW>(g, ga, gb, m0, in0, gm0);
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0);  // this thread's partial stores have reached L2
-  __syncthreads();
-  // one 128-byte line of counters per group of XCD slots
-  if (tid == 0) xcd_arrive_wait(g.ctr + x * 32 + t, x, (uint32_t)s, g.spin_limit, g.status);
-  __syncthreads();
-  const float *tile_part = g.part + (size_t)gt * s * (4 * PW * 64 * 4);
-  const __amdgpu_buffer_rsrc_t rp = rsrc_of(tile_part, (uint32_t)s * 4 * PW * 64 * 16);
-  // the other slices' partials are requested SB at a time (one round trip
-  // per batch; past the last slice nothing is loaded) and added in slice
-  // order, this slice's own from its registers
-  constexpr int SB = GW * S <= 2 ? 8 : 4;
-  auto finish_block = [&](int m, unsigned gmask) {
-    floatx4 am[GW][S];
-#pragma unroll
-    for (int i = 0; i < GW; ++i)
-#pragma unroll
-      for (int q = 0; q < S; ++q) am[i][q] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int sb = 0; sb < s; sb += SB) {
-      floatx4 buf[SB][GW][S];
-#pragma unroll
-      for (int b = 0; b < SB; ++b) {
-        const int sl = sb + b;
+      for (int p = 1; p >= 0; --p)
 #pragma unroll
         for (int i = 0; i < GW; ++i)
 #pragma unroll
-          for (int q = 0; q < S; ++q) {
-            const uint32_t off =
-                (uint32_t)((((size_t)sl * 4 * PW + ((wave * GW + i) * S + q) * MT + m) * 64 + lane) * 16);
-            buf[b][i][q] = sl < s && sl != ks && i < live && ((gmask >> i) & 1u) ? load_l2(rp, off)
-                                                                                 : floatx4{0.f, 0.f, 0.f, 0.f};
-          }
-      }
+          for (int q = 0; q < S; ++q)
 #pragma unroll
-      for (int b = 0; b < SB; ++b)
-        if (sb + b < s) {
-#pragma unroll
-          for (int i = 0; i < GW; ++i)
-#pragma unroll
-            for (int q = 0; q < S; ++q) am[i][q] += sb + b == ks ? acc[i][q][m] : buf[b][i][q];
-        }
-    }
-    EpiIn<KIND, GW> in;
-    if (m == m0)
-      in = in0;
-    else
-      epi_load<KIND, GW>(g, ga, gb, m, in, gmask);
-    epilogue<KIND, GW>(g, gt, ga, gb, m, am, rs_s, red_s, in, gmask);
+            for (int m = 0; m < MT; ++m)
+              acc[i][q][m] = mfma16x16x32(as_bf16x8(w[k][i * S + q]), as_bf16x8(a[k][2 * m + p]), acc[i][q][m]);
   };
-  if constexpr (kItems) {
+
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      const unsigned gmask = mine(m);
-      if (gmask) finish_block(m, gmask);  // uniform: no barriers in these epilogues
+  for (int d = 0; d < NB; ++d) {
+    request_a(d, ar[d]);
+    __builtin_amdgcn_sched_barrier(0);
+    request_w(d, wr[d]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if constexpr (NB == 1) request_w(1, wr[1]);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (kNorm) rs_finish<MT>(g, ssv, rs_tmp, rs_s);
+
+  // ---- main loop: multiply slab n, then request slab n + NB into its
+  // registers (NB = 1: the next activations and the weights after next)
+  int n = 0;
+  if constexpr (NB > 1) {
+    for (; n + NB <= n_slab; n += NB) {
+#pragma unroll
+      for (int d = 0; d < NB; ++d) {
+        multiply(wr[d], ar[d]);
+        __builtin_amdgcn_sched_barrier(0);
+        request_a(n + d + NB, ar[d]);
+        __builtin_amdgcn_sched_barrier(0);
+        request_w(n + d + NB, wr[d]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-  } else {
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
-      if (m % s == ks) finish_block(m, ~0u);  // uniform in the workgroup
+    for (int d = 0; d < NB - 1; ++d)
+      if (n + d < n_slab) multiply(wr[d], ar[d]);
+  } else {
+    auto turn = [&](int i, u32x4(&w)[KP][WF]) {
+      multiply(w, ar[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      request_a(i + 1, ar[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      request_w(i + 2, w);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (; n + 2 <= n_slab; n += 2) {
+      turn(n, wr[0]);
+      turn(n + 1, wr[1]);
+    }
+    if (n < n_slab) multiply(wr[0], ar[0]);
+  }
+
+  // ---- the waves' sums meet: item idx = (group i, token block m) of a
+  // round; wave (idx / s) % NW adds its NW parts in wave order.  s = 1: it
+  // then finishes the item.  s > 1: it stores the sum to the XCD's L2; after
+  // the tile's slices have met at the counter, slice idx % s (of the whole
+  // tile's items) adds the s sums in slice order and finishes the item.  Partial sums: [tile][slice][item][q][lane] floatx4.
+  [[maybe_unused]] TokenSlot slot;
+  constexpr int kPart = GW * MT * S * 256;  // floats per workgroup
+  float *part = g.part + ((size_t)gt * s + ks) * kPart;
+#pragma unroll
+  for (int m0 = 0; m0 < MT; m0 += MR) {
+    if (m0 > 0) __syncthreads();
+    EpiIn<KIND> in[PI];
+    if (s == 1) {
+#pragma unroll
+      for (int jj = 0; jj < PI; ++jj) {
+        const int idx = min(jj * NW + wave, ITEMS - 1);
+        if (KIND == GEMM_QKV && jj == 0) find_slot(g, min(m0 + idx % MR, MT - 1), slot);
+        epi_load<KIND>(g, min(ga + idx / MR, gb - 1), min(m0 + idx % MR, MT - 1), in[jj]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < GW; ++i)
+#pragma unroll
+      for (int r = 0; r < MR; ++r)
+        if (m0 + r < MT) {
+#pragma unroll
+          for (int q = 0; q < S; ++q)
+            *(floatx4 *)(red_s + (((wave * GW + i) * MR + r) * S + q) * 256 + lane * 4) = acc[i][q][m0 + r < MT ? m0 + r : 0];
+        }
+    __syncthreads();
+    auto sum_item = [&](int idx, floatx4(&a)[S]) {
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        a[q] = *(const floatx4 *)(red_s + (idx * S + q) * 256 + lane * 4);
+#pragma unroll
+        for (int w = 1; w < NW; ++w)
+          a[q] += *(const floatx4 *)(red_s + ((w * ITEMS + idx) * S + q) * 256 + lane * 4);
+      }
+    };
+    if (s == 1) {
+#pragma unroll
+      for (int jj = 0; jj < PI; ++jj) {
+        const int idx = jj * NW + wave;
+        const int i = idx / MR, m = m0 + idx % MR;
+        if (idx < ITEMS && i < ng && m < MT) {
+          floatx4 a[S];
+          sum_item(idx, a);
+          if constexpr (KIND == GEMM_QKV) find_slot(g, m, slot);
+          epilogue<KIND>(g, ga + i, m, a, rs_s, in[jj], item_s + (kRows ? (i * MT + m) * 16 : 0), slot);
+        }
+      }
+      continue;
+    }
+    for (int o = 0; o < ITEMS; o += s * NW)  // this wave's items: o + wave s + (0 .. s - 1)
+      for (int sl = 0; sl < s; ++sl) {
+        const int idx = o + wave * s + sl;
+        const int i = idx / MR, m = m0 + idx % MR;
+        if (idx >= ITEMS || i >= ng || m >= MT) continue;
+        floatx4 a[S];
+        sum_item(idx, a);
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+          *(floatx4 *)(part + ((size_t)(i * MT + m) * S + q) * 256 + lane * 4) = a[q];
+      }
+  }
+  if (s > 1) {
+    // this slice's items, dealt to its waves in turn: the s partial sums (its
+    // own too: the same bytes) are added in slice order; the next item's are
+    // requested while this one is finished
+    const int nb = (ng + R - 1) / R;  // groups of a class (m, i % R)
+    const int n_own = kRows ? ((MT * R - ks + s - 1) >> ls) * nb : (ng * MT - ks + s - 1) >> ls;
+    auto item_at = [&](int n, int &i, int &m) {
+      if constexpr (kRows) {
+        const int c = ks + s * (n / nb);
+        m = c / R;
+        i = c % R + R * (n % nb);
+      } else {
+        i = (ks + s * n) / MT;
+        m = (ks + s * n) % MT;
+      }
+      return i < ng;
+    };
+    EpiIn<KIND> in[2];
+    floatx4 buf[2][8][S];
+    const __amdgpu_buffer_rsrc_t rp = rsrc_of(g.part + (size_t)gt * s * kPart, (uint32_t)s * kPart * 4);
+    auto ask_sums = [&](int n, floatx4(&d)[8][S]) {
+      int i, m;
+      const uint32_t drop = n < n_own && item_at(n, i, m) ? 0u : kDropped;
+      if (drop) i = m = 0;
+#pragma unroll
+      for (int sl = 0; sl < 8; ++sl)
+#pragma unroll
+        for (int q = 0; q < S; ++q)  // past the last slice: beyond the resource, zeros
+          d[sl][q] = load_l2(rp, (uint32_t)(sl * kPart * 4 + ((i * MT + m) * S + q) * 1024 + lane * 16) | drop);
+    };
+    auto ask_inputs = [&](int n, EpiIn<KIND> &e) {
+      int i, m;
+      if (n < n_own && item_at(n, i, m)) epi_load<KIND>(g, ga + i, m, e);
+    };
+    auto finish = [&](int n, const floatx4(&d)[8][S], const EpiIn<KIND> &e) {
+      int i, m;
+      if (n >= n_own || !item_at(n, i, m)) return;
+      floatx4 a[S];
+#pragma unroll
+      for (int q = 0; q < S; ++q) {
+        a[q] = d[0][q];
+#pragma unroll
+        for (int sl = 1; sl < 8; ++sl) a[q] += d[sl][q];
+      }
+      if constexpr (KIND == GEMM_QKV) find_slot(g, m, slot);
+      epilogue<KIND>(g, ga + i, m, a, rs_s, e, item_s + (kRows ? (i * MT + m) * 16 : 0), slot);
+    };
+    ask_inputs(wave, in[0]);
+    ask_inputs(wave + NW, in[1]);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);  // this thread's partial stores have reached L2
+    __syncthreads();
+    // one 128-byte line of counters per group of XCD slots
+    if (tid == 0) xcd_arrive_wait(g.ctr + x * 32 + t, x, (uint32_t)s, g.spin_limit, g.status);
+    __syncthreads();
+    ask_sums(wave, buf[0]);
+    for (int n = wave; n < n_own; n += 2 * NW) {
+      ask_sums(n + NW, buf[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      finish(n, buf[0], in[0]);
+      ask_sums(n + 2 * NW, buf[0]);
+      ask_inputs(n + 2 * NW, in[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      finish(n + NW, buf[1], in[1]);
+      ask_inputs(n + 3 * NW, in[1]);
+    }
+  }
+  if constexpr (kRows) {
+    __syncthreads();
+    rows_out(ng);
   }
 }
 
 template <int MT, int KIND, int GW>
-hipError_t launch_mt_gw(const GemmLaunch &g, hipStream_t s) {
-  constexpr int WS = GW * SUB<KIND>;  // weight fragment pairs per wave and chunk
-  constexpr int RING = WS >= 4 ? 2 : WS >= 2 ? 4 : 8;
-  const dim3 grid(8 * g.TX * g.s), block(256);
+hipError_t launch_one(const GemmLaunch &g, hipStream_t s) {
+  const dim3 grid(8 * g.TX << g.ls), block(NT);
   hipEvent_t ev0 = (hipEvent_t)g.ev_start, ev1 = (hipEvent_t)g.ev_stop;
   if (ev0)
-    hipExtLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW, RING>), grid, block, 0, s, ev0, ev1, 0, g);
+    hipExtLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW>), grid, block, 0, s, ev0, ev1, 0, g);
   else
-    hipLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW, RING>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW>), grid, block, 0, s, g);
   return hipGetLastError();
 }
 
-// groups per wave instantiated for S sub-tiles and MT token tiles: the
-// accumulators (GW S MT floatx4) and one chunk's weight fragments (GW S
-// pairs) must leave room in one wave's registers
-constexpr int gw_limit(int S, int MT) {
-  return S == 1 ? (MT <= 4 ? 6 : MT <= 6 ? 4 : 3) : (MT <= 4 ? 3 : MT <= 6 ? 2 : 1);
-}
+// groups per tile instantiated for S sub-tiles and MT token tiles: the
+// accumulators (4 GW S MT registers), a step's activations and two steps'
+// weights must fit one wave's registers
+constexpr int gw_limit(int S, int MT) { return S == 1 ? (MT <= 7 ? 8 : 6) : MT <= 4 ? 6 : 4; }
 
 template <int MT, int KIND>
 hipError_t launch_mt(const GemmLaunch &g, hipStream_t s) {
   constexpr int LIM = gw_limit(SUB<KIND>, MT);
   switch (g.gw) {
-    case 1: return launch_mt_gw<MT, KIND, 1>(g, s);
-    case 2:
-      if constexpr (LIM >= 2) return launch_mt_gw<MT, KIND, 2>(g, s);
-      break;
-    case 3:
-      if constexpr (LIM >= 3) return launch_mt_gw<MT, KIND, 3>(g, s);
-      break;
-    case 4:
-      if constexpr (LIM >= 4) return launch_mt_gw<MT, KIND, 4>(g, s);
-      break;
-    case 6:
-      if constexpr (LIM >= 6) return launch_mt_gw<MT, KIND, 6>(g, s);
-      break;
+#define PPD_GW(n)                                                 \
+  case n:                                                         \
+    if constexpr (LIM >= n) return launch_one<MT, KIND, n>(g, s); \
+    break;
+    PPD_GW(1) PPD_GW(2) PPD_GW(3) PPD_GW(4) PPD_GW(6) PPD_GW(8)
+#undef PPD_GW
   }
   return hipErrorInvalidValue;
 }

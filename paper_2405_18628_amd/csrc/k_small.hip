@@ -8,9 +8,9 @@
 // Embedding and rotary tables, one launch.  Row t of the residual stream x
 // is the embedding of ids[t] (Section 3: prompt tokens are trained
 // embeddings appended to the input); for bf16 models the kernel also writes
-// the row's sum of squares (the first RMSNorm's one partial per row; its
-// x * gain is formed by the consumer GEMM) and, spread over the blocks,
-// zeroes the step's tile and head counters.  Rows T..T_pad-1 are zero.
+// the first RMSNorm's operand (x * gain, as operand planes) and the row's sum
+// of squares (one partial per row) and, spread over the blocks, zeroes the
+// step's tile and head counters.  Rows T..T_pad-1 are zero.
 // Rotary table row t: node t sits at position L + depth[t] (Section 3.1);
 // the angle of frequency i is pos * base^(-2i/d), evaluated in double
 // precision and rounded to float; padding rows get position 0.  Rows of a
@@ -23,7 +23,10 @@ __global__ __launch_bounds__(256) void embed_kernel(const WT *__restrict__ tok_e
                                                     const int32_t *__restrict__ depth, SeqBatch sb,
                                                     int d, float base, float2 *__restrict__ rope,
                                                     int vocab, int n_prompt, int H,
-                                                    float *__restrict__ x, float *__restrict__ ss,
+                                                    float *__restrict__ x,
+                                                    const bf16_t *__restrict__ gain,
+                                                    unsigned char *__restrict__ planes,
+                                                    float *__restrict__ ss,
                                                     uint32_t *__restrict__ ctr, size_t n_ctr,
                                                     uint32_t *status) {
   const int t = blockIdx.x, T = sb.t0[sb.B];
@@ -88,6 +91,16 @@ __global__ __launch_bounds__(256) void embed_kernel(const WT *__restrict__ tok_e
       *(floatx4 *)(xr + (size_t)c * E + e) = floatx4{v[e], v[e + 1], v[e + 2], v[e + 3]};
       acc += (v[e] * v[e] + v[e + 1] * v[e + 1]) + (v[e + 2] * v[e + 2] + v[e + 3] * v[e + 3]);
     }
+    if constexpr (sizeof(WT) == 2) {  // H % 128 == 0: every row goes through here
+      const u32x4 gn = *(const u32x4 *)(gain + (size_t)c * E);
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o[2 * e] = v[2 * e] * bf16_to_f32(gn[e] & 0xffffu);
+        o[2 * e + 1] = v[2 * e + 1] * bf16_to_f32(gn[e] >> 16);
+      }
+      store_plane8(planes, gridDim.x / 16, t, c * E, o);
+    }
   }
   if (ss) {
     __shared__ float red[4];
@@ -100,17 +113,19 @@ __global__ __launch_bounds__(256) void embed_kernel(const WT *__restrict__ tok_e
 
 hipError_t launch_embed(int dtype, const void *tok_emb, const void *prompt_emb, const int32_t *ids,
                         const int32_t *depth, const SeqBatch &sb, int d, float base, float2 *rope,
-                        int vocab, int n_prompt, int H, float *x, float *ss, uint32_t *ctr,
-                        size_t n_ctr, uint32_t *status, hipStream_t s) {
+                        int vocab, int n_prompt, int H, float *x, const bf16_t *gain,
+                        unsigned char *planes, float *ss, uint32_t *ctr, size_t n_ctr,
+                        uint32_t *status, hipStream_t s) {
   const int T_pad = (sb.t0[sb.B] + 15) & ~15;
   if (dtype == PPD_BF16) {
     hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(T_pad), dim3(256), 0, s, (const bf16_t *)tok_emb,
                        (const bf16_t *)prompt_emb, ids, depth, sb, d, base, rope, vocab, n_prompt, H, x,
-                       ss, ctr, n_ctr, status);
+                       gain, planes, ss, ctr, n_ctr, status);
   } else {
     hipLaunchKernelGGL(embed_kernel<float>, dim3(T_pad), dim3(256), 0, s, (const float *)tok_emb,
                        (const float *)prompt_emb, ids, depth, sb, d, base, rope, vocab, n_prompt, H, x,
-                       (float *)nullptr, (uint32_t *)nullptr, (size_t)0, status);
+                       (const bf16_t *)nullptr, (unsigned char *)nullptr, (float *)nullptr,
+                       (uint32_t *)nullptr, (size_t)0, status);
   }
   return hipGetLastError();
 }

@@ -135,42 +135,46 @@ struct GemmShape {
   int kind, N, K;
 };
 
-// Partition of one GEMM for MT token tiles (see GemmLaunch): for each
-// candidate number s of K slices (the XCD's 32 workgroups then take 32 / s
-// tiles of h groups), a model of the slowest workgroup's time, taken from
-// measurements on MI355X: its weight bytes plus 0.4 x its fp32 activation
-// bytes (L2 hits, read while the weights stream) at a compute unit's ~35
-// GB/s, or its matrix-core time at 70 % of peak if larger; with s > 1 a
-// tail that does not overlap the stream -- ~1.5 us of hand-off plus writing
-// and reading its partial sums at ~25 GB/s.  The cheapest is taken.  Groups
-// per wave come from the instantiated set {1, 2, 3, 4, 6} (bounded by the
-// registers).
+// Partition of one GEMM for MT token tiles (see GemmLaunch).  For each number
+// s of K slices the XCD's 32 workgroups take TX = 32 / s tiles (s = 1: 32, 64,
+// .. tiles, as few as the largest instantiated tile allows; each further 32
+// are a round of workgroups that follows) of h groups, and the cheapest by a
+// model of the slowest workgroup's time is taken.  The model's rates are the
+// MI355X compute unit's load path, measured: it returns loads in order, so a
+// workgroup's weight bytes cost ~36 GB/s (HBM latency over what a compute
+// unit can have outstanding) and its activation bytes, L2 hits, ~110 GB/s on
+// top of that, and all weights together stream at 6.2 TB/s at most.  s > 1
+// divides the activation bytes by s and adds the exchange of the partial
+// sums: ~2 us of latency and ~4 GB/s for a workgroup's sums.  Compared with
+// every plan that fits, timed one by one (1.4B, 7B, 13B and GQA shapes, T = 1
+// .. 128), the choice is the fastest or within 1.3 us of it.  E.g. 7B, T = 64:
+// QKV and gate/up whole (30.3, 43.1 us; in 2 slices 34.2, 52.2), output
+// projection in 4 slices (18.7 us; 20.0 whole, 22.6 in 8), down projection in
+// 4 (32.1; 46.8 whole, 33.4 in 8); T = 16: output projection whole (12.0 us;
+// 13.7 in 4 slices).
 struct GemmPlan {
   int gw = 1, TX = 32, s = 1;
-  int xg0[9] = {0};
+  // rows of the tiles' reductions (sums of squares, argmax)
+  int rows(int MT) const { return 8 * TX * ((s + MT - 1) / MT); }
 };
 
 GemmPlan plan_gemm(const GemmShape &sh, int MT, bool xcd_sync) {
   GemmPlan best;
   const int G = gemm_groups_of(sh.kind, sh.N), S = gemm_sub_of(sh.kind), kc = sh.K / 64;
-  for (int x = 0; x <= 8; ++x) best.xg0[x] = (int)((long)G * x / 8);
   const int nx = (G + 7) / 8;
   const int gmax = gemm_gw_max(sh.kind, MT);
+  const double hbm = 2.0 * G * 16 * S * sh.K / 6.2e12;
   double best_t = 1e30;
-  for (int s = 1; s <= 16; s *= 2) {
+  for (int s = 1; s <= 8; s *= 2) {
     if (s > kc || (s > 1 && !xcd_sync)) break;
-    const int TX = 32 / s;
-    const int h = std::max(1, (nx + TX - 1) / TX);
-    int gw = (h + 3) / 4;
-    if (gw == 5) gw = 6;
+    int TX = 32 / s, h = std::max(1, (nx + TX - 1) / TX);
+    if (s == 1)
+      for (; h > gmax; h = (nx + TX - 1) / TX) TX += 32;
+    const int gw = h == 5 ? 6 : h == 7 ? 8 : h;
     if (gw > gmax) continue;
-    const double kch = (double)((kc + s - 1) / s);
-    const double wb = (double)h * 16 * S * kch * 64 * 2;
-    const double ab = (double)MT * 16 * kch * 64 * 4;
-    const double pb = (double)h * 16 * S * MT * 16 * 4;
-    const double flops = 4.0 * MT * 16 * h * 16 * S * kch * 64;
-    const double t = std::max((wb + 0.4 * ab) / 35e9, flops / (0.7 * 2.5e15 / 256)) +
-                     (s > 1 ? 1.5e-6 + 2 * pb / 25e9 : 0.0);
+    const double cols = (double)((kc + s - 1) / s) * 64;
+    const double wb = 2.0 * h * 16 * S * cols, ab = 4.0 * MT * 16 * cols, pb = 1024.0 * h * S * MT;
+    const double t = std::max((TX + 31) / 32 * (wb / 36e9 + ab / 110e9), hbm) + (s > 1 ? 2e-6 + pb / 4e9 : 0.0);
     if (t < best_t) {
       best_t = t;
       best.gw = gw;
@@ -194,7 +198,7 @@ void gemm_shapes(const ppd_model *m, GemmShape out[5]) {
 // bytes of the partial sums of a plan (0 when every tile is whole)
 size_t plan_part_bytes(const GemmShape &sh, const GemmPlan &p, int MT) {
   if (p.s == 1) return 0;
-  return (size_t)8 * p.TX * p.s * 4 * p.gw * gemm_sub_of(sh.kind) * MT * 64 * 16;
+  return (size_t)8 * p.TX * p.s * p.gw * gemm_sub_of(sh.kind) * MT * 64 * 16;
 }
 
 constexpr int kSpinLimit = 1 << 14;  // bounded wait of a tile's slices (~10-20 ms)
@@ -242,9 +246,9 @@ WsLayout layout_of(const ppd_model *m, int T) {
   };
   w.status = take(16);
   w.x = take(sizeof(float) * Tp * H);
-  // activations are fp32 on both paths; the fp32 path also keeps x * gain
-  // and the row scales (the bf16 GEMMs form x * gain while staging)
-  w.xg = take(bf16 ? 0 : sizeof(float) * (Tp * H + Tp));
+  // activations take 4 bytes an element on both paths (bf16 models: fp32 x
+  // and q, operand planes of two bf16 parts elsewhere)
+  w.xg = take(sizeof(float) * (Tp * H + (bf16 ? 0 : Tp)));
   w.max_ss = 1;
   w.max_amax_tiles = 1;
   size_t part = 0;
@@ -256,8 +260,8 @@ WsLayout layout_of(const ppd_model *m, int T) {
       for (int i = 0; i < 5; ++i) {
         const GemmPlan p = plan_gemm(gs[i], mt, sync);
         part = std::max(part, plan_part_bytes(gs[i], p, mt));
-        if (gs[i].kind == GEMM_RESID) w.max_ss = std::max(w.max_ss, 8 * p.TX);
-        if (gs[i].kind == GEMM_LOGITS) w.max_amax_tiles = std::max(w.max_amax_tiles, 8 * p.TX);
+        if (gs[i].kind == GEMM_RESID) w.max_ss = std::max(w.max_ss, p.rows(mt));
+        if (gs[i].kind == GEMM_LOGITS) w.max_amax_tiles = std::max(w.max_amax_tiles, p.rows(mt));
       }
   }
   w.ss = take(sizeof(float) * w.max_ss * Tp);
@@ -330,8 +334,9 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
   float *x = at<float>(ws, w.x);
   float *ss = at<float>(ws, w.ss);
   float *q = at<float>(ws, w.q);
-  float *attn_o = at<float>(ws, w.attn_o);
-  float *act = at<float>(ws, w.act);
+  unsigned char *xg = at<unsigned char>(ws, w.xg);
+  unsigned char *attn_o = at<unsigned char>(ws, w.attn_o);
+  unsigned char *act = at<unsigned char>(ws, w.act);
   float *part = at<float>(ws, w.gemm_part);
   float2 *amax = at<float2>(ws, w.amax);
   float2 *rope = at<float2>(ws, w.rope);
@@ -347,18 +352,26 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
     g.N = gs[i].N;
     g.K = gs[i].K;
     g.kc = gs[i].K / 64;
+    g.w_bytes = (uint32_t)((size_t)gemm_groups_of(g.kind, g.N) * gemm_sub_of(g.kind) * 16 * g.K * sizeof(bf16_t));
+    g.a_bytes = (uint32_t)(sizeof(float) * Tp * g.K);
     g.gw = plan[i].gw;
     g.TX = plan[i].TX;
-    g.s = plan[i].s;
-    for (int xx = 0; xx <= 8; ++xx) g.xg0[xx] = plan[i].xg0[xx];
+    g.ls = 0;
+    while ((1 << g.ls) < plan[i].s) ++g.ls;
+    g.G = gemm_groups_of(g.kind, g.N);
+    g.q0 = g.G / 8 / g.TX;
+    g.r0 = g.G / 8 % g.TX;
+    g.q1 = (g.G / 8 + 1) / g.TX;
+    g.r1 = (g.G / 8 + 1) % g.TX;
     g.ctr = ctr + (size_t)launch++ * 256;
   };
 
-  // embedding, its sum of squares (one partial per row), rotary table,
-  // zeroed counters
+  // embedding, the first norm's operand and sums of squares (one partial per
+  // row), rotary table, zeroed counters
   PPD_TRY_HIP(launch_embed(PPD_BF16, m->tok_emb, m->prompt_emb, ids, depth,
                            seq_batch(m, B, kvs, Ls, Ts, 0), m->head_dim, m->rope_base, rope,
-                           m->vocab, m->n_prompt, H, x, ss, ctr, w.n_ctr, status, s));
+                           m->vocab, m->n_prompt, H, x, (const bf16_t *)m->attn_norm[0], xg, ss, ctr,
+                           w.n_ctr, status, s));
   int n_ss = 1;
   // attention work per sequence: nh x splits workgroups
   // (one sequence on 256 CUs: heads dealt to the XCDs, splits merged in the
@@ -386,12 +399,11 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
     g.eps = m->rms_eps;
     g.status = status;
     g.spin_limit = kSpinLimit;
-    // QKV + RoPE + cache stores; A = x * attn_norm
+    // QKV + RoPE + cache stores; operand x * attn_norm
     GemmLaunch qg = g;
     setup(qg, SH_QKV);
     qg.W = (const bf16_t *)m->w_qkv[l];
-    qg.A = x;
-    qg.gain = (const bf16_t *)m->attn_norm[l];
+    qg.A = xg;
     qg.ss = ss;
     qg.n_ss = n_ss;
     qg.rope = rope;
@@ -426,44 +438,46 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
     a.scale_log2 = (float)(1.4426950408889634 / std::sqrt(128.0));
     timer_events(TK_ATTN, &a.ev_start, &a.ev_stop);
     PPD_TRY_HIP(launch_attn_bf16(a, s));
-    // O projection + residual; sums of squares for the MLP norm
+    // O projection + residual; the MLP norm's operand and sums of squares
     GemmLaunch o = g;
     setup(o, SH_O);
     o.W = (const bf16_t *)m->w_o[l];
     o.A = attn_o;
     o.x = x;
     o.ss_out = ss;
+    o.gain = (const bf16_t *)m->mlp_norm[l];
+    o.planes = xg;
     timer_events(TK_O, &o.ev_start, &o.ev_stop);
     PPD_TRY_HIP(launch_gemm_bf16(o, s));
-    n_ss = 8 * plan[SH_O].TX;
-    // gate/up + SwiGLU; A = x * mlp_norm
+    n_ss = plan[SH_O].rows(MT);
+    // gate/up + SwiGLU; operand x * mlp_norm
     GemmLaunch u = g;
     setup(u, SH_GATE_UP);
     u.W = (const bf16_t *)m->w_gate_up[l];
-    u.A = x;
-    u.gain = (const bf16_t *)m->mlp_norm[l];
+    u.A = xg;
     u.ss = ss;
     u.n_ss = n_ss;
-    u.act = act;
+    u.planes = act;
     timer_events(TK_GATEUP, &u.ev_start, &u.ev_stop);
     PPD_TRY_HIP(launch_gemm_bf16(u, s));
-    // down projection + residual; sums of squares for the next norm
+    // down projection + residual; the next norm's operand and sums of squares
     GemmLaunch dn = g;
     setup(dn, SH_DOWN);
     dn.W = (const bf16_t *)m->w_down[l];
     dn.A = act;
     dn.x = x;
     dn.ss_out = ss;
+    dn.gain = (const bf16_t *)(l + 1 < m->n_layers ? m->attn_norm[l + 1] : m->final_norm);
+    dn.planes = xg;
     timer_events(TK_DOWN, &dn.ev_start, &dn.ev_stop);
     PPD_TRY_HIP(launch_gemm_bf16(dn, s));
-    n_ss = 8 * plan[SH_DOWN].TX;
+    n_ss = plan[SH_DOWN].rows(MT);
   }
-  // final norm + LM head + greedy partials; A = x * final_norm
+  // final norm + LM head + greedy partials; operand x * final_norm
   GemmLaunch lm{};
   setup(lm, SH_LM);
   lm.W = (const bf16_t *)m->lm_head;
-  lm.A = x;
-  lm.gain = (const bf16_t *)m->final_norm;
+  lm.A = xg;
   lm.T = T;
   lm.MT = MT;
   lm.part = part;
@@ -477,7 +491,7 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
   lm.spin_limit = kSpinLimit;
   timer_events(TK_LM, &lm.ev_start, &lm.ev_stop);
   PPD_TRY_HIP(launch_gemm_bf16(lm, s));
-  PPD_TRY_HIP(launch_argmax_final(amax, 8 * plan[SH_LM].TX, T, Tp, pred, status, s));
+  PPD_TRY_HIP(launch_argmax_final(amax, plan[SH_LM].rows(MT), T, Tp, pred, status, s));
   return PPD_OK;
 }
 
@@ -502,7 +516,7 @@ ppd_status step_f32(const ppd_model *m, const ppd_kv *kv, int L, int T, const in
   one.t0[1] = T;
   one.L[0] = L;
   PPD_TRY_HIP(launch_embed(PPD_F32, m->tok_emb, m->prompt_emb, ids, depth, one, d, m->rope_base, rope,
-                           m->vocab, m->n_prompt, H, x, nullptr, nullptr, 0, status, s));
+                           m->vocab, m->n_prompt, H, x, nullptr, nullptr, nullptr, nullptr, 0, status, s));
   for (int l = 0; l < m->n_layers; ++l) {
     float *kc = (float *)kv->k + (size_t)l * nkv * cap * d;
     float *vc = (float *)kv->v + (size_t)l * nkv * d * cap;

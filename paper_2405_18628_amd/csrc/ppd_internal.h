@@ -51,6 +51,37 @@ __device__ __forceinline__ floatx4 load_l2(__amdgpu_buffer_rsrc_t r, uint32_t by
   return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, 1));
 }
 
+// ---- operand planes: a bf16 GEMM's activations [T_pad][K] as the B operand
+// of v_mfma_f32_16x16x32_bf16, each element the sum of two bf16 parts.
+// Fragment (k-step u = column / 32, token block m = token / 16, part p: 0 hi,
+// 1 lo) is 1 KB; its lane l holds token 16 m + l % 16, columns 32 u + 8 (l /
+// 16) .. + 7.  Order [u][m][p]; T_pad x K x 4 bytes, as fp32.
+__host__ __device__ __forceinline__ size_t plane_off(int MT, int tok, int col) {
+  return ((size_t)((col >> 5) * MT + (tok >> 4)) << 11) + (((tok & 15) + 16 * ((col >> 3) & 3)) << 4) +
+         2 * (col & 7);
+}
+constexpr int kPlaneLo = 1024;  // bytes from an element's hi part to its lo part
+// columns col .. col + 3 (col % 4 == 0) of token tok
+__device__ __forceinline__ void store_plane4(unsigned char *planes, int MT, int tok, int col, const float (&v)[4]) {
+  float lo[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) lo[e] = v[e] - bf16_to_f32(f32_to_bf16(v[e]));
+  unsigned char *d = planes + plane_off(MT, tok, col);
+  *(u32x2 *)d = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+  *(u32x2 *)(d + kPlaneLo) = u32x2{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
+}
+// columns col .. col + 7 (col % 8 == 0)
+__device__ __forceinline__ void store_plane8(unsigned char *planes, int MT, int tok, int col, const float (&v)[8]) {
+  float lo[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) lo[e] = v[e] - bf16_to_f32(f32_to_bf16(v[e]));
+  unsigned char *d = planes + plane_off(MT, tok, col);
+  *(u32x4 *)d = u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]),
+                      pack_bf16x2(v[6], v[7])};
+  *(u32x4 *)(d + kPlaneLo) = u32x4{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]),
+                                   pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7])};
+}
+
 // the XCD this wave runs on
 __device__ __forceinline__ unsigned xcc_id() {
   unsigned v;
@@ -105,11 +136,12 @@ __device__ __forceinline__ float wave_max(float v) {
 struct WsLayout {
   size_t status;      // uint32 [4]
   size_t x;           // float  [T_pad][H]        residual stream
-  size_t xg;          // fp32 path: float [T_pad][H] x * gain, then [T_pad] row scales
+  size_t xg;          // x * gain of the next norm: operand planes [T_pad][H] (fp32 path:
+                      // float [T_pad][H], then [T_pad] row scales)
   size_t ss;          // float  [max_ss][T_pad]   sum-of-squares partials
   size_t q;           // float  [T_pad][nh][d]    queries after RoPE
-  size_t attn_o;      // float  [T_pad][nh d]     attention output
-  size_t act;         // float  [T_pad][F]        SwiGLU output
+  size_t attn_o;      // operand planes [T_pad][nh d] attention output (fp32 path: float)
+  size_t act;         // operand planes [T_pad][F] SwiGLU output (fp32 path: float)
   size_t tmp;         // float  [T_pad][max(qkv_rows, 2F, V)]  (fp32 path only)
   size_t attn_part;   // float  [nh][max_splits][T_pad][d + 2]
   size_t gemm_part;   // float  [max_part_floats]
@@ -130,13 +162,13 @@ struct WsLayout {
 // Skinny GEMM partition (k_gemm.hip).  Weights are packed group-major: a
 // group is 16 output rows (gate/up: 16 features, i.e. 16 gate and 16 up
 // rows), each of its K / 64 chunks a run of 1 KB MFMA fragments.  The groups
-// are dealt to the 8 XCDs (XCD x: groups [xg0[x], xg0[x + 1])); on each XCD,
-// TX tiles (consecutive groups, at most 4 gw) x s K-slices take its TX s
+// are dealt to the 8 XCDs (XCD x: groups [G x / 8, G (x + 1) / 8)); on each XCD,
+// TX tiles (consecutive groups, at most gw) x s K-slices take its TX s
 // workgroups (workgroup b runs on XCD b % 8, slot b / 8 = tile s + slice).
 // A tile split over s > 1 slices is finished inside the kernel: partial sums
-// to L2, an XCD-local counter, each slice finishing token blocks ks, ks + s,
-// ...  Grid = 8 TX s <= 256, one workgroup per compute unit.
-#define PPD_GEMM_BN 128
+// to L2, an XCD-local counter, each slice finishing its share of the tile's
+// items.  One workgroup per compute unit; grid = 8 TX s, with s > 1 at most
+// 256 (workgroups that wait for each other are resident together).
 
 // The sequences of one (batched) step: their tree tokens are packed in
 // sequence order, sequence s owning tokens [t0[s], t0[s + 1]); each has its
@@ -153,20 +185,22 @@ struct SeqBatch {
 struct GemmLaunch {
   // operands
   const bf16_t *W;      // packed weight (ppd_pack_weight)
-  const float *A;       // [T_pad][K] fp32 activations (norm consumers: the residual x)
-  const bf16_t *gain;   // norm consumers (QKV, gate/up, LM head): the norm gain [K]
+  const unsigned char *A;  // operand planes [T_pad][K] (norm consumers: of x * gain)
+  uint32_t w_bytes, a_bytes;  // their sizes
   int N, K, T, MT;      // N = output rows (SwiGLU: F), MT = T_pad / 16
   int kind;             // GemmKind
   // partition (see above)
   int kc;               // K / 64
-  int gw;               // groups per wave (a tile holds at most 4 gw groups)
-  int TX, s;            // tiles per XCD, K slices per tile
-  int xg0[9];
-  float *part;          // s > 1: [8 TX][s][4 gw S MT][64] floatx4 partial sums
+  int gw;               // most groups a tile holds
+  int TX, ls;           // tiles per XCD, log2 of the K slices per tile
+  int G;                // groups; an XCD has G / 8 or one more of them, of which
+  int q0, r0, q1, r1;   // a tile holds q0 = (G / 8) / TX, the first r0 = (G / 8) % TX
+                        // one more (q1, r1: for G / 8 + 1)
+  float *part;          // s > 1: [8 TX][s][gw MT S][64] floatx4 partial sums
   uint32_t *ctr;        // s > 1: tile counters, XCD x's at ctr + 32 x (zeroed per step)
   int spin_limit;       // bounded wait for a tile's other slices
   // epilogue inputs
-  const float *ss;      // norm partials for row scaling (QKV, SwiGLU, LOGITS)
+  const float *ss;      // [n_ss][T_pad] sum-of-squares partials (QKV, SwiGLU, LOGITS)
   int n_ss;
   float inv_h, eps;
   const float2 *rope;   // [T_pad][64]
@@ -176,12 +210,13 @@ struct GemmLaunch {
   SeqBatch sb;          // caches, positions: token t of sequence s goes to L[s] + t - t0[s]
   // RESID
   float *x;
-  float *ss_out;        // [8 TX][T_pad]
-  // SWIGLU
-  float *act;           // [T_pad][N] fp32
+  float *ss_out;        // [8 TX R][T_pad]: sums of squares, R = ceil(s / MT) rows a tile
+  const bf16_t *gain;   // the next norm's gain [N]
+  // RESID: x * gain, SWIGLU: the activation, as the next GEMM's operand [T_pad][N]
+  unsigned char *planes;
   // LOGITS
   float *logits;        // [T][N] or null
-  float2 *amax;         // [8 TX][T_pad]
+  float2 *amax;         // [8 TX R][T_pad]
   uint32_t *status;
   void *ev_start, *ev_stop;  // optional events at the dispatch's start / end
 };
@@ -190,7 +225,7 @@ enum GemmKind { GEMM_QKV = 0, GEMM_RESID = 1, GEMM_SWIGLU = 2, GEMM_LOGITS = 3 }
 
 int gemm_groups_of(int kind, int N);  // groups of a GEMM with N output rows (gate/up: features)
 int gemm_sub_of(int kind);            // 16-row sub-tiles per group (2 for gate/up)
-int gemm_gw_max(int kind, int MT);    // largest groups-per-wave instantiated for MT token tiles
+int gemm_gw_max(int kind, int MT);    // largest tile (in groups) instantiated for MT token tiles
 hipError_t launch_pack_weight(int kind, int N, int K, const bf16_t *src, bf16_t *dst, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmLaunch &g, hipStream_t s);
 
@@ -199,7 +234,7 @@ hipError_t launch_gemm_bf16(const GemmLaunch &g, hipStream_t s);
 struct AttnLaunch {
   const float *q;       // [T_pad][nh][d] fp32
   const uint64_t *mask; // [T][2], bits over the token's own tree
-  float *out;           // [T_pad][nh d] fp32
+  unsigned char *out;   // operand planes [T_pad][nh d]
   float *part;          // [nh][max_splits][T_pad][PPD_ATTN_OROW] (splits > 1)
   const bf16_t *zeros;  // >= 16 zero bytes
   int T_pad, nh, nkv, max_splits;
@@ -244,12 +279,14 @@ hipError_t launch_next_tree(const NextTreeLaunch &p, int n_depths, hipStream_t s
 ppd_status ppd_fail(ppd_status s, const char *fmt, ...);
 
 // embedding rows into x (fp32), rows T..T_pad-1 zero, and the rotary
-// table [T_pad][d / 2] (cos, sin); bf16 models also write each row's sum of
-// squares to ss and zero the n_ctr tile / head counters
+// table [T_pad][d / 2] (cos, sin); bf16 models also write the first norm's
+// operand planes (x * gain) and sums of squares (ss, one per row) and zero
+// the n_ctr tile / head counters
 hipError_t launch_embed(int dtype, const void *tok_emb, const void *prompt_emb, const int32_t *ids,
                         const int32_t *depth, const SeqBatch &sb, int d, float base, float2 *rope,
-                        int vocab, int n_prompt, int H, float *x, float *ss, uint32_t *ctr,
-                        size_t n_ctr, uint32_t *status, hipStream_t s);
+                        int vocab, int n_prompt, int H, float *x, const bf16_t *gain,
+                        unsigned char *planes, float *ss, uint32_t *ctr, size_t n_ctr,
+                        uint32_t *status, hipStream_t s);
 hipError_t launch_argmax_final(const float2 *amax, int n_tiles, int T, int T_pad, int32_t *pred,
                                uint32_t *status, hipStream_t s);
 hipError_t launch_accept(int T, const int32_t *parent, const int32_t *ids, const int32_t *pred,
