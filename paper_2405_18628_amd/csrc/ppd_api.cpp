@@ -248,9 +248,9 @@ WsLayout layout_of(const ppd_model *m, int T) {
   w.x = take(sizeof(float) * Tp * H);
   // activations take 4 bytes an element on both paths (bf16 models: fp32 x
   // and q, operand planes of two bf16 parts elsewhere)
-  w.xg = take(sizeof(float) * (Tp * H + (bf16 ? 0 : Tp)));
+  w.xg = take(bf16 ? sizeof(float) * Tp * H : 0);
   w.max_ss = 1;
-  w.max_amax_tiles = 1;
+  w.max_amax_tiles = bf16 ? 1 : (m->vocab + 15) / 16;
   size_t part = 0;
   if (bf16) {
     GemmShape gs[5];
@@ -268,12 +268,6 @@ WsLayout layout_of(const ppd_model *m, int T) {
   w.q = take(sizeof(float) * Tp * nh * d);
   w.attn_o = take(sizeof(float) * Tp * nh * d);
   w.act = take(sizeof(float) * Tp * F);
-  if (!bf16) {
-    const size_t wide = std::max({(size_t)qkv_rows(m), (size_t)2 * F, (size_t)H, (size_t)m->vocab});
-    w.tmp = take(sizeof(float) * Tp * wide);
-  } else {
-    w.tmp = take(0);
-  }
   w.max_splits = bf16 ? attn_max_splits(nh) : 0;
   w.attn_part = take(sizeof(float) * (size_t)nh * w.max_splits * Tp * PPD_ATTN_OROW);
   w.max_part_floats = part / sizeof(float);
@@ -499,16 +493,13 @@ ppd_status step_f32(const ppd_model *m, const ppd_kv *kv, int L, int T, const in
                     const int32_t *depth, const uint64_t *mask, void *ws, const WsLayout &w,
                     float *logits, int32_t *pred, hipStream_t s) {
   const int H = m->hidden, F = m->ffn, nh = m->n_heads, nkv = m->n_kv_heads, d = m->head_dim;
-  const int Tp = t_pad_of(T);
   const int cap = kv->capacity;
   uint32_t *status = at<uint32_t>(ws, w.status);
   float *x = at<float>(ws, w.x);
-  float *xg = at<float>(ws, w.xg);
-  float *r = xg + (size_t)Tp * H;
   float *q = at<float>(ws, w.q);
   float *attn_o = at<float>(ws, w.attn_o);
   float *act = at<float>(ws, w.act);
-  float *tmp = at<float>(ws, w.tmp);
+  float2 *amax = at<float2>(ws, w.amax);
   float2 *rope = at<float2>(ws, w.rope);
 
   SeqBatch one{};
@@ -517,27 +508,38 @@ ppd_status step_f32(const ppd_model *m, const ppd_kv *kv, int L, int T, const in
   one.L[0] = L;
   PPD_TRY_HIP(launch_embed(PPD_F32, m->tok_emb, m->prompt_emb, ids, depth, one, d, m->rope_base, rope,
                            m->vocab, m->n_prompt, H, x, nullptr, nullptr, nullptr, nullptr, 0, status, s));
+  F32Gemm g{};
+  g.T = T;
+  g.eps = m->rms_eps;
+  g.rope = rope;
+  g.nh = nh;
+  g.nkv = nkv;
+  g.d = d;
+  g.cap = cap;
+  g.L = L;
+  g.status = status;
+  auto gemm = [&](int kind, const float *A, const void *W, const void *gain, int N, int K, float *out) {
+    g.kind = kind;
+    g.A = A;
+    g.W = (const float *)W;
+    g.gain = (const float *)gain;
+    g.N = N;
+    g.K = K;
+    g.out = out;
+    return launch_f32_gemm(g, s);
+  };
   for (int l = 0; l < m->n_layers; ++l) {
-    float *kc = (float *)kv->k + (size_t)l * nkv * cap * d;
-    float *vc = (float *)kv->v + (size_t)l * nkv * d * cap;
-    PPD_TRY_HIP(launch_f32_rownorm(x, (const float *)m->attn_norm[l], T, H, m->rms_eps, xg, s));
-    PPD_TRY_HIP(launch_f32_matmul_scaled(xg, (const float *)m->w_qkv[l], T, qkv_rows(m), H, r,
-                                         tmp, s));
-    PPD_TRY_HIP(launch_f32_qkv_post(tmp, rope, T, nh, nkv, d, q, kc, vc, cap, L, s));
-    PPD_TRY_HIP(launch_f32_attention(q, kc, vc, mask, T, L, cap, nh, nkv, d, attn_o, s));
-    PPD_TRY_HIP(launch_f32_matmul(attn_o, (const float *)m->w_o[l], T, H, nh * d, tmp, s));
-    PPD_TRY_HIP(launch_f32_add(x, tmp, T * H, s));
-    PPD_TRY_HIP(launch_f32_rownorm(x, (const float *)m->mlp_norm[l], T, H, m->rms_eps, xg, s));
-    PPD_TRY_HIP(launch_f32_matmul_scaled(xg, (const float *)m->w_gate_up[l], T, 2 * F, H, r, tmp,
-                                         s));
-    PPD_TRY_HIP(launch_f32_swiglu(tmp, T, F, act, s));
-    PPD_TRY_HIP(launch_f32_matmul(act, (const float *)m->w_down[l], T, H, F, tmp, s));
-    PPD_TRY_HIP(launch_f32_add(x, tmp, T * H, s));
+    g.kc = (float *)kv->k + (size_t)l * nkv * cap * d;
+    g.vc = (float *)kv->v + (size_t)l * nkv * d * cap;
+    PPD_TRY_HIP(gemm(GEMM_QKV, x, m->w_qkv[l], m->attn_norm[l], qkv_rows(m), H, q));
+    PPD_TRY_HIP(launch_f32_attention(q, g.kc, g.vc, mask, T, L, cap, nh, nkv, d, attn_o, s));
+    PPD_TRY_HIP(gemm(GEMM_RESID, attn_o, m->w_o[l], nullptr, H, nh * d, x));
+    PPD_TRY_HIP(gemm(GEMM_SWIGLU, x, m->w_gate_up[l], m->mlp_norm[l], F, H, act));
+    PPD_TRY_HIP(gemm(GEMM_RESID, act, m->w_down[l], nullptr, H, F, x));
   }
-  PPD_TRY_HIP(launch_f32_rownorm(x, (const float *)m->final_norm, T, H, m->rms_eps, xg, s));
-  float *lg = logits ? logits : tmp;
-  PPD_TRY_HIP(launch_f32_matmul_scaled(xg, (const float *)m->lm_head, T, m->vocab, H, r, lg, s));
-  PPD_TRY_HIP(launch_f32_argmax(lg, T, m->vocab, pred, status, s));
+  g.amax = amax;
+  PPD_TRY_HIP(gemm(GEMM_LOGITS, x, m->lm_head, m->final_norm, m->vocab, H, logits));
+  PPD_TRY_HIP(launch_argmax_final(amax, (m->vocab + 15) / 16, T, t_pad_of(T), pred, status, s));
   return PPD_OK;
 }
 

@@ -136,13 +136,11 @@ __device__ __forceinline__ float wave_max(float v) {
 struct WsLayout {
   size_t status;      // uint32 [4]
   size_t x;           // float  [T_pad][H]        residual stream
-  size_t xg;          // x * gain of the next norm: operand planes [T_pad][H] (fp32 path:
-                      // float [T_pad][H], then [T_pad] row scales)
+  size_t xg;          // x * gain of the next norm: operand planes [T_pad][H] (bf16 models)
   size_t ss;          // float  [max_ss][T_pad]   sum-of-squares partials
   size_t q;           // float  [T_pad][nh][d]    queries after RoPE
   size_t attn_o;      // operand planes [T_pad][nh d] attention output (fp32 path: float)
   size_t act;         // operand planes [T_pad][F] SwiGLU output (fp32 path: float)
-  size_t tmp;         // float  [T_pad][max(qkv_rows, 2F, V)]  (fp32 path only)
   size_t attn_part;   // float  [nh][max_splits][T_pad][d + 2]
   size_t gemm_part;   // float  [max_part_floats]
   size_t amax;        // float2 [max_amax_tiles][T_pad]
@@ -298,20 +296,25 @@ hipError_t launch_kv_compact(int dtype, void *k, void *v, int n_layers, int nkv,
 hipError_t launch_ws_init(void *ws, size_t n_words, hipStream_t s);
 hipError_t launch_read_probe(const void *buf, size_t bytes, uint32_t *sink, hipStream_t s);
 
-// fp32 path (simple kernels for float32 models)
-// xg = x * gain and r[t] = 1/sqrt(mean(x^2)+eps); r is stored after xg's T_pad rows
-hipError_t launch_f32_rownorm(const float *x, const float *gain, int T, int H, float eps,
-                              float *xg, hipStream_t s);
-hipError_t launch_f32_matmul(const float *A, const float *W, int T, int N, int K, float *out,
-                             hipStream_t s);
-hipError_t launch_f32_matmul_scaled(const float *A, const float *W, int T, int N, int K,
-                                    const float *r, float *out, hipStream_t s);
-hipError_t launch_f32_qkv_post(const float *qkv, const float2 *rope, int T, int nh, int nkv, int d,
-                               float *q, float *kc, float *vc, int cap, int L, hipStream_t s);
+// fp32 path (float32 models): one product with its neighbours fused, kinds as
+// GemmKind
+struct F32Gemm {
+  int kind;
+  const float *A;     // [T_pad][K]
+  const float *W;     // row-major [N][K] (SwiGLU: [2 N][K], gate rows then up rows)
+  const float *gain;  // norm kinds: the norm gain [K]
+  int T, N, K;
+  float eps;
+  float *out;  // QKV: q [T][nh][d]; RESID: x [T][N], added to; SwiGLU: [T][N]; LOGITS: [T][N] or null
+  // QKV
+  const float2 *rope;
+  float *kc, *vc;
+  int nh, nkv, d, cap, L;
+  // LOGITS: best (value, index) of each 16 rows, [ceil(N / 16)][T_pad]
+  float2 *amax;
+  uint32_t *status;
+};
+hipError_t launch_f32_gemm(const F32Gemm &g, hipStream_t s);
 hipError_t launch_f32_attention(const float *q, const float *kc, const float *vc,
                                 const uint64_t *mask, int T, int L, int cap, int nh, int nkv,
                                 int d, float *out, hipStream_t s);
-hipError_t launch_f32_add(float *x, const float *y, int n, hipStream_t s);
-hipError_t launch_f32_swiglu(const float *gu, int T, int F, float *act, hipStream_t s);
-hipError_t launch_f32_argmax(const float *logits, int T, int V, int32_t *pred, uint32_t *status,
-                             hipStream_t s);

@@ -1,0 +1,72 @@
+"""GPU parity where the kernels' tilings can go wrong: matrices with fewer row
+groups than XCDs, ragged groups, column counts that leave a wave without a
+step, projections split over 2 to 8 workgroups, one to eight token tiles; and
+the float32 path with sizes that rule out its 16-byte loads.  Every node's
+logits against the oracle within the tolerances of gpu_cases (bf16 2e-2 + 1e-2
+|o|, float32 1e-4 + 1e-4 |o|)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2405_18628_amd as ppd
+from gpu_cases import check_logits, check_pred, gpu_step, make_case, oracle_step, tree_for, workspace
+from synth.configs import ModelShape, Workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(dtype, hidden, heads, kv, d, ffn, vocab, L, cap=None, layers=2):
+    sh = ModelShape(f"edge-{dtype}-{hidden}-{ffn}", layers, hidden, heads, kv, d, ffn, vocab, dtype)
+    return make_case(Workload("edge", sh, L, "total:16", 5, "normal", 50), capacity=cap)
+
+
+def _check(case, spec):
+    tree = tree_for(case, spec=spec)
+    ws = workspace(case, tree.T)
+    res, ref = gpu_step(case, tree, ws), oracle_step(case, tree)
+    assert ppd.ppd_device_status(ws) == 0
+    check_logits(res["logits"], ref["logits"], case.shape.dtype, f"T={tree.T}")
+    check_pred(res["pred"], ref["logits"], case.shape.dtype)
+
+
+@pytest.mark.parametrize("shape", [
+    (128, 1, 1, 64, 7),        # 4 gate/up groups and 1 LM-head group for 8 XCDs
+    (640, 5, 1, 448, 333),     # 10 and 7 chunks of columns, ragged groups
+    (384, 8, 2, 1152, 1000),   # 18 chunks: slices of 2 and 3
+    (2048, 16, 16, 5632, 500),  # the 1.4B widths: output / down split 2, 4, 8 ways
+])
+@pytest.mark.parametrize("specs", [("chain:1", "total:33", "total:80"), ("total:16", "total:50", "total:128")])
+def test_bf16_tilings(shape, specs):
+    hidden, heads, kv, ffn, vocab = shape
+    case = _case("bf16", hidden, heads, kv, 128, ffn, vocab, 70, layers=1 if hidden > 1000 else 2)
+    for spec in specs:
+        _check(case, spec)
+
+
+@pytest.mark.parametrize("hidden,heads,kv,d,ffn,vocab,L,cap,spec", [
+    (256, 4, 4, 64, 688, 1000, 128, 256, "total:25"),  # 16-byte loads everywhere
+    (66, 3, 1, 22, 77, 101, 37, 61, "total:17"),       # none: rows of 66 and 77, head 22, capacity 61
+    (40, 2, 2, 20, 36, 37, 5, 9, "chain:1"),           # one node and its chain
+    (128, 1, 1, 128, 64, 16, 300, 431, "total:128"),   # the widest head, eight token tiles
+    (60, 2, 1, 30, 44, 50, 0, 8, "total:7"),           # no prefix; head rows unaligned, matrix rows aligned
+])
+def test_f32_sizes(hidden, heads, kv, d, ffn, vocab, L, cap, spec):
+    _check(_case("f32", hidden, heads, kv, d, ffn, vocab, L, cap), spec)
+
+
+def test_f32_overflowed_node_stays_invisible():
+    """A node whose embedding is infinite changes no node that does not see it
+    (bit for bit), in the float32 path."""
+    case = _case("f32", 256, 4, 4, 64, 688, 1000, 40)
+    tree = tree_for(case, spec="total:25")
+    ws = workspace(case, tree.T)
+    clean = gpu_step(case, tree, ws)["logits"]
+    last = tree.T - 1  # the last node of the last prompt chain: nothing sees it
+    assert last not in tree.parent
+    tree.ids[last] = 999
+    assert not (np.delete(tree.ids, last) == 999).any()
+    case.W["tok_emb"][999].fill_(float("inf"))
+    torch.cuda.synchronize()
+    got = gpu_step(case, tree, ws)["logits"]
+    assert np.array_equal(got[:last], clean[:last])
+    assert not np.isfinite(got[last]).all()
