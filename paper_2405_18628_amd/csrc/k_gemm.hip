@@ -226,7 +226,7 @@ __device__ __forceinline__ void epilogue(const GemmLaunch &g, int grp, int m, co
     }
     if (tk >= T) return;
     if (hp < nh) {
-      *(floatx4 *)(g.q + ((size_t)tk * nh + hp) * 128 + d0) = floatx4{v[0], v[1], v[2], v[3]};
+      store_plane4(g.q, g.MT, tk, hp * 128 + d0, v);
       return;
     }
     const int cap = st.cap, pos = st.pos;

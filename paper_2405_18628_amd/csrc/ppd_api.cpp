@@ -203,34 +203,45 @@ size_t plan_part_bytes(const GemmShape &sh, const GemmPlan &p, int MT) {
 
 constexpr int kSpinLimit = 1 << 14;  // bounded wait of a tile's slices (~10-20 ms)
 
-// Key splits of the attention: a workgroup per (head, split) reads each
-// key/value block once, so the splits spread the cache over the compute
-// units -- about one workgroup per CU, each keeping at least 4 of the
-// 32-key blocks.
-// key splits per head: nh x splits workgroups must fit one round on the CUs
-// (one attention workgroup per CU), or the last ones run alone afterwards
+// Key splits of a head: at most what puts one workgroup of each of its XCD's
+// heads and splits on one of the XCD's 32 compute units.
 int attn_max_splits(int nh) { return std::max(1, std::min(PPD_ATTN_MAX_SPLITS, kCUs / nh)); }
 
-void attn_splits(const ppd_model *m, int L, int T, int *splits, int *chunk) {
-  const int nblk = (L + T + 31) / 32;
-  const int ks = std::max(1, std::min(attn_max_splits(m->n_heads), nblk / 4));
-  const int c = ((nblk + ks - 1) / ks + 1) & ~1;  // even: splits start on 64-key pairs
-  *splits = (nblk + c - 1) / c;
-  *chunk = c;
-}
+// The attention's key splits.  An XCD's heads x splits of all sequences must
+// fit its 32 compute units together, or nothing is split: the slots left are
+// given one by one to the sequence with the most blocks per split, as long as
+// a split keeps kAttnMinBlocks 32-key blocks; then each sequence takes the
+// fewest splits that need no more steps of the kernel.
+constexpr int kAttnMinBlocks = 4;
 
-// One sequence on 256 CUs: the heads are dealt to the 8 XCDs (at most
-// ceil(nh / 8) per XCD) and each head's splits take that XCD's 32 CUs
-// together (they merge through its L2), so a head gets up to
-// 32 / ceil(nh / 8) splits.  Returns the workgroup count (8 x heads per XCD
-// x splits).
-int attn_splits_xcd(const ppd_model *m, int L, int T, int *splits, int *chunk) {
-  const int nblk = (L + T + 31) / 32, hpx = (m->n_heads + 7) / 8;
-  const int ks = std::max(1, std::min(std::min(PPD_ATTN_MAX_SPLITS, 32 / hpx), nblk / 4));
-  const int c = ((nblk + ks - 1) / ks + 1) & ~1;  // even: splits start on 64-key pairs
-  *splits = (nblk + c - 1) / c;
-  *chunk = c;
-  return 8 * hpx * *splits;
+void plan_attn(AttnLaunch &a, bool xcd_sync) {
+  const int B = a.sb.B, unit = (a.nh + 7) / 8;
+  int nblk[PPD_BATCH_MAX], used = B * unit;
+  a.tiles = 1;
+  for (int j = 0; j < B; ++j) {
+    const int T = a.sb.t0[j + 1] - a.sb.t0[j];
+    a.tiles = std::max(a.tiles, (T + 15) / 16);
+    nblk[j] = (a.sb.L[j] + T + 31) / 32;
+    a.splits[j] = 1;
+  }
+  for (; xcd_sync && used + unit <= 32; used += unit) {
+    int best = -1;
+    for (int j = 0; j < B; ++j)
+      if (nblk[j] >= (a.splits[j] + 1) * kAttnMinBlocks && a.splits[j] < a.max_splits &&
+          (best < 0 || (long)nblk[j] * a.splits[best] > (long)nblk[best] * a.splits[j]))
+        best = j;
+    if (best < 0) break;
+    ++a.splits[best];
+  }
+  const int step = attn_blocks_per_step(a.tiles);
+  a.slot0[0] = 0;
+  for (int j = 0; j < B; ++j) {
+    const int per = (nblk[j] + a.splits[j] - 1) / a.splits[j];
+    a.chunk[j] = (per + step - 1) / step * step;
+    a.splits[j] = (nblk[j] + a.chunk[j] - 1) / a.chunk[j];
+    a.slot0[j + 1] = a.slot0[j] + unit * a.splits[j];
+    a.ctr0[j] = j * unit;  // used only with splits: then all slots fit 32, and so do the counters
+  }
 }
 
 WsLayout layout_of(const ppd_model *m, int T) {
@@ -318,16 +329,13 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
                      const uint64_t *mask, void *ws, const WsLayout &w, float *logits,
                      int32_t *pred, hipStream_t s) {
   const int H = m->hidden, nh = m->n_heads, nkv = m->n_kv_heads;
-  int T = 0, MT_seq = 1;
-  for (int j = 0; j < B; ++j) {
-    T += Ts[j];
-    MT_seq = std::max(MT_seq, (Ts[j] + 15) / 16);
-  }
+  int T = 0;
+  for (int j = 0; j < B; ++j) T += Ts[j];
   const int Tp = t_pad_of(T), MT = Tp / 16;
   uint32_t *status = at<uint32_t>(ws, w.status);
   float *x = at<float>(ws, w.x);
   float *ss = at<float>(ws, w.ss);
-  float *q = at<float>(ws, w.q);
+  unsigned char *q = at<unsigned char>(ws, w.q);
   unsigned char *xg = at<unsigned char>(ws, w.xg);
   unsigned char *attn_o = at<unsigned char>(ws, w.attn_o);
   unsigned char *act = at<unsigned char>(ws, w.act);
@@ -367,20 +375,21 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
                            m->vocab, m->n_prompt, H, x, (const bf16_t *)m->attn_norm[0], xg, ss, ctr,
                            w.n_ctr, status, s));
   int n_ss = 1;
-  // attention work per sequence: nh x splits workgroups
-  // (one sequence on 256 CUs: heads dealt to the XCDs, splits merged in the
-  // kernel; a batch: a merge kernel)
-  int splits[PPD_BATCH_MAX], chunk[PPD_BATCH_MAX], wg0[PPD_BATCH_MAX + 1] = {0};
-  const bool xcd_merge = B == 1 && sync && nh <= 256;
+  AttnLaunch a{};
+  a.q = q;
+  a.mask = mask;
+  a.out = attn_o;
+  a.part = at<float>(ws, w.attn_part);
+  a.T_pad = Tp;
+  a.nh = nh;
+  a.nkv = nkv;
+  a.max_splits = w.max_splits;
+  a.spin_limit = kSpinLimit;
+  a.status = status;
+  a.scale_log2 = (float)(1.4426950408889634 / std::sqrt(128.0));
+  a.sb = seq_batch(m, B, kvs, Ls, Ts, 0);
+  plan_attn(a, sync);
   uint32_t *attn_ctr = ctr + (size_t)(4 * m->n_layers + 1) * 256;
-  if (xcd_merge) {
-    wg0[1] = attn_splits_xcd(m, Ls[0], Ts[0], &splits[0], &chunk[0]);
-  } else {
-    for (int j = 0; j < B; ++j) {
-      attn_splits(m, Ls[j], Ts[j], &splits[j], &chunk[j]);
-      wg0[j + 1] = wg0[j] + nh * splits[j];
-    }
-  }
   const float inv_h = 1.0f / (float)H;
 
   for (int l = 0; l < m->n_layers; ++l) {
@@ -408,28 +417,8 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
     timer_events(TK_QKV, &qg.ev_start, &qg.ev_stop);
     PPD_TRY_HIP(launch_gemm_bf16(qg, s));
     // tree attention
-    AttnLaunch a{};
-    a.q = q;
-    a.mask = mask;
-    a.out = attn_o;
-    a.part = at<float>(ws, w.attn_part);
-    a.zeros = (const bf16_t *)((const char *)ws + PPD_WS_ZEROS);
-    a.T_pad = Tp;
-    a.nh = nh;
-    a.nkv = nkv;
-    a.max_splits = w.max_splits;
-    a.MT = MT_seq;
     a.sb = sb;
-    for (int j = 0; j < B; ++j) {
-      a.splits[j] = splits[j];
-      a.chunk[j] = chunk[j];
-    }
-    for (int j = 0; j <= B; ++j) a.wg0[j] = wg0[j];
-    a.xcd_merge = xcd_merge;
     a.ctr = attn_ctr + (size_t)l * 256;
-    a.spin_limit = kSpinLimit;
-    a.status = status;
-    a.scale_log2 = (float)(1.4426950408889634 / std::sqrt(128.0));
     timer_events(TK_ATTN, &a.ev_start, &a.ev_stop);
     PPD_TRY_HIP(launch_attn_bf16(a, s));
     // O projection + residual; the MLP norm's operand and sums of squares

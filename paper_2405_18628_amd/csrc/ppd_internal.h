@@ -138,7 +138,7 @@ struct WsLayout {
   size_t x;           // float  [T_pad][H]        residual stream
   size_t xg;          // x * gain of the next norm: operand planes [T_pad][H] (bf16 models)
   size_t ss;          // float  [max_ss][T_pad]   sum-of-squares partials
-  size_t q;           // float  [T_pad][nh][d]    queries after RoPE
+  size_t q;           // operand planes [T_pad][nh d] queries after RoPE (fp32 path: float)
   size_t attn_o;      // operand planes [T_pad][nh d] attention output (fp32 path: float)
   size_t act;         // operand planes [T_pad][F] SwiGLU output (fp32 path: float)
   size_t attn_part;   // float  [nh][max_splits][T_pad][d + 2]
@@ -203,7 +203,7 @@ struct GemmLaunch {
   float inv_h, eps;
   const float2 *rope;   // [T_pad][64]
   // QKV outputs
-  float *q;             // [T_pad][nh][128] fp32
+  unsigned char *q;     // operand planes [T_pad][nh 128]
   int nh, nkv;
   SeqBatch sb;          // caches, positions: token t of sequence s goes to L[s] + t - t0[s]
   // RESID
@@ -230,29 +230,27 @@ hipError_t launch_gemm_bf16(const GemmLaunch &g, hipStream_t s);
 #define PPD_ATTN_OROW 132  // floats per partial row: 128 dims, m, l, padding
 
 struct AttnLaunch {
-  const float *q;       // [T_pad][nh][d] fp32
+  const unsigned char *q;  // operand planes [T_pad][nh d]
   const uint64_t *mask; // [T][2], bits over the token's own tree
   unsigned char *out;   // operand planes [T_pad][nh d]
   float *part;          // [nh][max_splits][T_pad][PPD_ATTN_OROW] (splits > 1)
-  const bf16_t *zeros;  // >= 16 zero bytes
   int T_pad, nh, nkv, max_splits;
-  int MT;               // largest query-tile count of a sequence
+  int tiles;            // most 16-query tiles of a sequence
   SeqBatch sb;
-  // sequence s: workgroups [wg0[s], wg0[s + 1]) = nh x splits[s], chunk[s]
-  // 32-key blocks per split
-  int wg0[PPD_BATCH_MAX + 1], splits[PPD_BATCH_MAX], chunk[PPD_BATCH_MAX];
-  // xcd_merge (one sequence): the heads are dealt to the 8 XCDs (XCD x:
-  // heads [nh x / 8, nh (x + 1) / 8), workgroup b runs on XCD b % 8, slot
-  // b / 8 = local head splits + split), and each head's splits merge inside
-  // the kernel through L2 behind the head's counter, ctr + 32 x + local head
-  // (zeroed per step); otherwise a merge kernel adds them
-  int xcd_merge;
+  // Workgroup b: XCD set x = b % 8 (heads [nh x / 8, nh (x + 1) / 8)), slot
+  // b / 8; sequence s takes slots [slot0[s], slot0[s + 1]) = ceil(nh / 8) heads
+  // x splits[s], a split holding chunk[s] 32-key blocks.  A head's splits meet
+  // at counter ctr + 32 x + ctr0[s] + local head (zeroed per step); splits > 1
+  // only where all slots of an XCD fit its 32 compute units (they wait for each
+  // other).
+  int slot0[PPD_BATCH_MAX + 1], splits[PPD_BATCH_MAX], chunk[PPD_BATCH_MAX], ctr0[PPD_BATCH_MAX];
   uint32_t *ctr;
   int spin_limit;
   uint32_t *status;
   float scale_log2;     // log2(e) / sqrt(d)
-  void *ev_start, *ev_stop;  // optional events at the first dispatch's start / last one's end
+  void *ev_start, *ev_stop;  // optional events at the dispatch's start / end
 };
+int attn_blocks_per_step(int tiles);  // blocks a workgroup multiplies together
 hipError_t launch_attn_bf16(const AttnLaunch &a, hipStream_t s);
 
 // next-step candidate generation (k_next.hip)
