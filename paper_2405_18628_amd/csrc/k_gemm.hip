@@ -95,8 +95,8 @@ __device__ __forceinline__ int group_row(int grp, int q, int r, int N) {
 // ---- RMSNorm row scale r[t] = 1/sqrt(mean(x^2) + eps) from the producer's
 // partial sums of squares ss[p][T_pad], p < n_ss: thread (quad of tokens,
 // residue j) adds partials j, j + NJ, .. in order, then the NJ sums are added
-// in order.  The first RS_N partials of a thread are requested ahead of the
-// weight ring (rs_request), so they arrive while it fills.
+// in order.  The first RS_N partials of a thread are requested between the
+// first slabs (rs_request).
 constexpr int RS_N = 8;
 
 template <int MT>
@@ -393,9 +393,6 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
     return;
   }
 
-  [[maybe_unused]] floatx4 ssv[RS_N];
-  if constexpr (kNorm) rs_request<MT>(g, ssv);
-
   // ---- the wave's k-steps u0 + (slab NW + wave) KP + k, k < KP: weight
   // fragments (group i, sub-tile q) and activation fragments (token block m,
   // part p).  Steps past the slice and groups past the tile are dropped loads
@@ -458,11 +455,17 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
               acc[i][q][m] = mfma16x16x32(as_bf16x8(w[k][i * S + q]), as_bf16x8(a[k][2 * m + p]), acc[i][q][m]);
   };
 
+  [[maybe_unused]] floatx4 ssv[RS_N];
 #pragma unroll
   for (int d = 0; d < NB; ++d) {
     request_a(d, ar[d]);
     __builtin_amdgcn_sched_barrier(0);
     request_w(d, wr[d]);
+    __builtin_amdgcn_sched_barrier(0);
+    // behind the first slab: the stream starts first, and the row scales wait
+    // for no more than the first products do
+    if constexpr (kNorm)
+      if (d == 0) rs_request<MT>(g, ssv);
     __builtin_amdgcn_sched_barrier(0);
   }
   if constexpr (NB == 1) request_w(1, wr[1]);

@@ -180,32 +180,32 @@ struct SeqBatch {
   bf16_t *v[PPD_BATCH_MAX];   // this layer's values [nkv][128][cap]
 };
 
+// (What a workgroup needs before its first load comes first: few cache lines
+// of kernel arguments.)
 struct GemmLaunch {
   // operands
   const bf16_t *W;      // packed weight (ppd_pack_weight)
   const unsigned char *A;  // operand planes [T_pad][K] (norm consumers: of x * gain)
   uint32_t w_bytes, a_bytes;  // their sizes
-  int N, K, T, MT;      // N = output rows (SwiGLU: F), MT = T_pad / 16
-  int kind;             // GemmKind
   // partition (see above)
   int kc;               // K / 64
-  int gw;               // most groups a tile holds
   int TX, ls;           // tiles per XCD, log2 of the K slices per tile
   int G;                // groups; an XCD has G / 8 or one more of them, of which
   int q0, r0, q1, r1;   // a tile holds q0 = (G / 8) / TX, the first r0 = (G / 8) % TX
                         // one more (q1, r1: for G / 8 + 1)
+  // norm partials for row scaling (QKV, SwiGLU, LOGITS): [n_ss][T_pad]
+  int n_ss;
+  const float *ss;
+  float inv_h, eps;
+  int N, K, T, MT;      // N = output rows (SwiGLU: F), MT = T_pad / 16
   float *part;          // s > 1: [8 TX][s][gw MT S][64] floatx4 partial sums
   uint32_t *ctr;        // s > 1: tile counters, XCD x's at ctr + 32 x (zeroed per step)
+  uint32_t *status;
   int spin_limit;       // bounded wait for a tile's other slices
-  // epilogue inputs
-  const float *ss;      // [n_ss][T_pad] sum-of-squares partials (QKV, SwiGLU, LOGITS)
-  int n_ss;
-  float inv_h, eps;
-  const float2 *rope;   // [T_pad][64]
   // QKV outputs
-  unsigned char *q;     // operand planes [T_pad][nh 128]
   int nh, nkv;
-  SeqBatch sb;          // caches, positions: token t of sequence s goes to L[s] + t - t0[s]
+  const float2 *rope;   // [T_pad][64]
+  unsigned char *q;     // operand planes [T_pad][nh 128]
   // RESID
   float *x;
   float *ss_out;        // [8 TX R][T_pad]: sums of squares, R = ceil(s / MT) rows a tile
@@ -215,7 +215,10 @@ struct GemmLaunch {
   // LOGITS
   float *logits;        // [T][N] or null
   float2 *amax;         // [8 TX R][T_pad]
-  uint32_t *status;
+  SeqBatch sb;          // QKV: caches, positions: token t of sequence s goes to L[s] + t - t0[s]
+  // host side
+  int kind;             // GemmKind
+  int gw;               // most groups a tile holds
   void *ev_start, *ev_stop;  // optional events at the dispatch's start / end
 };
 
