@@ -106,14 +106,56 @@ def _check(status: int):
 
 
 def _ptr(t) -> int:
-    return 0 if t is None else int(t.data_ptr())
+    return 0 if t is None else t.data_ptr()
+
+
+# The small calls after a forward pass are bound by this module's host time
+# (accept, compact and next tree: 34 us of Python for 20 us of kernels), so
+# what every call does is kept short: the current stream's handle comes from
+# torch's raw getters (0.2 us; building a torch.cuda.Stream takes 2.5), and
+# the tensor checks take one pass (_i32_ok), with _dev naming the fault.
+_torch = None
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        global _torch
+        if _torch is None:
+            import torch
+            torch.cuda.init()
+            _torch = torch
+        c = _torch._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
     return getattr(stream, "cuda_stream", stream)
+
+
+def _i32_ok(tensors) -> bool:
+    """Every tensor is a contiguous int32 device tensor."""
+    try:
+        for t in tensors:
+            if not (t.is_cuda and t.dtype is _torch.int32 and t.is_contiguous()):
+                return False
+        return True
+    except AttributeError:  # None, or torch not loaded yet: the full check decides
+        return False
+
+
+def _i32(**tensors):
+    if not _i32_ok(tensors.values()):
+        import torch
+        for name, t in tensors.items():
+            _dev(t, torch.int32, name)
+
+
+def _host_i32(v):
+    """`v` as a contiguous int32 numpy array (no copy if it is one)."""
+    if type(v) is np.ndarray and v.dtype == np.int32 and v.flags.c_contiguous:
+        return v
+    return np.ascontiguousarray(np.asarray(v, dtype=np.int32))
+
+
+def _np_ptr(a) -> int:
+    return a.__array_interface__["data"][0]
 
 
 def _dev(t, dtype=None, name="tensor"):
@@ -251,8 +293,7 @@ def ppd_build_tree_mask(parent: Sequence[int]):
 def ppd_verify_step(model: Model, kv: KVCache, L: int, T: int, ids, depth, mask, ws, logits,
                     pred, stream=None):
     import torch
-    for t, n in ((ids, "ids"), (depth, "depth"), (pred, "pred")):
-        _dev(t, torch.int32, n)
+    _i32(ids=ids, depth=depth, pred=pred)
     _dev(mask, None, "mask")
     _dev(ws, None, "ws")
     _dev(logits, torch.float32, "logits")
@@ -299,10 +340,7 @@ def ppd_verify_batch(model: Model, kvs: Sequence[KVCache], L: Sequence[int], T: 
 
 
 def ppd_accept(T: int, parent, ids, pred, vocab: int, path, n_path, next_tok, ws, stream=None):
-    import torch
-    for t, n in ((parent, "parent"), (ids, "ids"), (pred, "pred"), (path, "path"),
-                 (n_path, "n_path"), (next_tok, "next_tok")):
-        _dev(t, torch.int32, n)
+    _i32(parent=parent, ids=ids, pred=pred, path=path, n_path=n_path, next_tok=next_tok)
     _check(lib().ppd_accept(int(T), _ptr(parent), _ptr(ids), _ptr(pred), int(vocab), _ptr(path),
                             _ptr(n_path), _ptr(next_tok), _ptr(ws), ws.numel() * ws.element_size(),
                             _stream(stream)))
@@ -314,17 +352,15 @@ def ppd_next_tree(T: int, parent, ids, vocab: int, n_prompt: int, logits, path, 
     """Token ids of the next step's tree (template tpl_parent / tpl_kind, host
     sequences) into the device tensor next_ids."""
     import torch
-    for t, n in ((parent, "parent"), (ids, "ids"), (path, "path"), (n_path, "n_path"),
-                 (next_tok, "next_tok"), (next_ids, "next_ids")):
-        _dev(t, torch.int32, n)
+    _i32(parent=parent, ids=ids, path=path, n_path=n_path, next_tok=next_tok, next_ids=next_ids)
     _dev(logits, torch.float32, "logits")
-    tp = np.ascontiguousarray(np.asarray(tpl_parent, dtype=np.int32))
-    tk = np.ascontiguousarray(np.asarray(tpl_kind, dtype=np.int32))
+    tp = _host_i32(tpl_parent)
+    tk = _host_i32(tpl_kind)
     if tp.shape != tk.shape:
         raise ValueError("tpl_parent and tpl_kind differ in length")
     _check(lib().ppd_next_tree(int(T), _ptr(parent), _ptr(ids), int(vocab), int(n_prompt),
                                int(n_ept), _ptr(logits), _ptr(path), _ptr(n_path), _ptr(next_tok),
-                               int(tp.shape[0]), tp.ctypes.data, tk.ctypes.data, _ptr(next_ids),
+                               int(tp.shape[0]), _np_ptr(tp), _np_ptr(tk), _ptr(next_ids),
                                _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)))
 
 
@@ -349,9 +385,7 @@ def ppd_kv_compact(model: Model, kv: KVCache, L: int, path, n_path, stream=None,
                    path_len: Optional[int] = None):
     """path: device int32 tensor (its length is passed as path_len unless
     given); n_path: device int32 count, clamped on the device."""
-    import torch
-    _dev(path, torch.int32, "path")
-    _dev(n_path, torch.int32, "n_path")
+    _i32(path=path, n_path=n_path)
     n = int(path.numel()) if path_len is None else int(path_len)
     _check(lib().ppd_kv_compact(C.byref(model.desc), C.byref(kv.desc), int(L), _ptr(path), n,
                                 _ptr(n_path), _stream(stream)))
