@@ -148,8 +148,9 @@ def _i32(**tensors):
 
 
 def _host_i32(v):
-    """`v` as a contiguous int32 numpy array (no copy if it is one)."""
-    if type(v) is np.ndarray and v.dtype == np.int32 and v.flags.c_contiguous:
+    """`v` as a contiguous int32 numpy array (no copy if it is one; a scalar
+    becomes an array of one)."""
+    if type(v) is np.ndarray and v.ndim and v.dtype == np.int32 and v.flags.c_contiguous:
         return v
     return np.ascontiguousarray(np.asarray(v, dtype=np.int32))
 

@@ -189,6 +189,17 @@ def test_next_tree_rejects_before_enqueue():
     assert call([-1, 0, 0], [0, 0, -3], n_ept=2) == ppd.PPD_EINVAL   # distance 2 under the root
 
 
+@pytest.mark.parametrize("v", [
+    [3, 1, 2], np.arange(6, dtype=np.int32), np.arange(6, dtype=np.int32)[::2], np.arange(6),
+    np.arange(6, dtype=">i4"), np.array(4, np.int32), np.zeros(0, np.int32)])
+def test_host_template_forms(v):
+    """Every form of a host template reaches the library as numpy's own
+    conversion gives it: contiguous int32, at least one dimension."""
+    got, want = ppd._host_i32(v), np.ascontiguousarray(np.asarray(v, dtype=np.int32))
+    assert got.dtype == np.int32 and got.dtype.isnative and got.flags.c_contiguous
+    assert got.shape == want.shape and np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("depth_max,k_max,n_cand,n_prompt,n_ept,seed", [
     (3, 16, 15, 3, 1, 0), (3, 16, 31, 3, 1, 1), (3, 16, 0, 3, 1, 2), (2, 3, 12, 2, 1, 3),
     (4, 5, 20, 3, 1, 4), (3, 16, 7, 3, 2, 5), (1, 16, 16, 3, 1, 6), (3, 16, 24, 3, 1, 7),
