@@ -258,7 +258,7 @@ ppd_status ppd_accept(int32_t T, const int32_t *parent, const int32_t *ids,
  * bits), the header of the array being cleared at the start of every call.
  * PPD_EWORKSPACE when the step needs more than PPD_STATIC_WS_BYTES
  * (ppd_workspace_bytes(model, T, capacity); a Vicuna-13B-shaped step needs
- * about 15 MiB with a 64-node tree, 30 MiB with 128), nothing enqueued.  All
+ * about 22 MiB with a 64-node tree, 43 MiB with 128), nothing enqueued.  All
  * calls on one GPU share the array: calls that may overlap on one GPU
  * (unordered streams, several threads) race and must not be made.
  */

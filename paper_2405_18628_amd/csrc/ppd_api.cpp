@@ -257,9 +257,14 @@ WsLayout layout_of(const ppd_model *m, int T) {
   };
   w.status = take(16);
   w.x = take(sizeof(float) * Tp * H);
-  // activations take 4 bytes an element on both paths (bf16 models: fp32 x
-  // and q, operand planes of two bf16 parts elsewhere)
-  w.xg = take(bf16 ? sizeof(float) * Tp * H : 0);
+  // activations take 4 bytes an element on both paths (bf16 models: fp32 x,
+  // operand planes of two bf16 parts elsewhere).  x * gain lives from the GEMM
+  // that writes it to the one that reads it, the attention's split rows within
+  // one launch between the two: they share memory, so that a step needs no
+  // more of it for the operand planes
+  w.max_splits = bf16 ? attn_max_splits(nh) : 0;
+  const size_t split_rows = sizeof(float) * (size_t)nh * w.max_splits * Tp * PPD_ATTN_OROW;
+  w.xg = w.attn_part = take(bf16 ? std::max(sizeof(float) * Tp * H, split_rows) : 0);
   w.max_ss = 1;
   w.max_amax_tiles = bf16 ? 1 : (m->vocab + 15) / 16;
   size_t part = 0;
@@ -279,8 +284,6 @@ WsLayout layout_of(const ppd_model *m, int T) {
   w.q = take(sizeof(float) * Tp * nh * d);
   w.attn_o = take(sizeof(float) * Tp * nh * d);
   w.act = take(sizeof(float) * Tp * F);
-  w.max_splits = bf16 ? attn_max_splits(nh) : 0;
-  w.attn_part = take(sizeof(float) * (size_t)nh * w.max_splits * Tp * PPD_ATTN_OROW);
   w.max_part_floats = part / sizeof(float);
   w.gemm_part = take(part);
   w.amax = take(sizeof(float2) * w.max_amax_tiles * Tp);

@@ -141,7 +141,7 @@ struct WsLayout {
   size_t q;           // operand planes [T_pad][nh d] queries after RoPE (fp32 path: float)
   size_t attn_o;      // operand planes [T_pad][nh d] attention output (fp32 path: float)
   size_t act;         // operand planes [T_pad][F] SwiGLU output (fp32 path: float)
-  size_t attn_part;   // float  [nh][max_splits][T_pad][d + 2]
+  size_t attn_part;   // float  [nh][max_splits][T_pad][PPD_ATTN_OROW]; the same memory as xg
   size_t gemm_part;   // float  [max_part_floats]
   size_t amax;        // float2 [max_amax_tiles][T_pad]
   size_t rope;        // float2 [T_pad][d/2]      (cos, sin)
