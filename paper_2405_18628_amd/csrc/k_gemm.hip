@@ -331,7 +331,7 @@ constexpr int slab_bufs(int MT, int WF) {
 // ---- the GEMM.  Workgroup b: XCD x = b % 8, slot j = b / 8 -> tile
 // t = j / s (groups [ga, gb) of the XCD's range, at most GW), K slice
 // ks = j % s (k-steps [u0, u1)).
-template <int MT, int KIND, int GW>
+template <int MT, int KIND, int GW, bool FEW>
 __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
   constexpr int T_pad = MT * 16;
   constexpr int S = SUB<KIND>, WF = GW * S;
@@ -405,6 +405,8 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
     wo[i] = i < ng ? lane * 16 : kDropped;
     wg[i] = min(ga + i, gb - 1) * kc * 2 * S;
   }
+  // FEW: lanes of padding tokens load nothing
+  const uint32_t ao = !FEW || (lane & 15) < g.T ? lane * 16 : kDropped;
   const int n_slab = __builtin_amdgcn_readfirstlane((u1 - u0 + NW * KP - 1) / (NW * KP));
   u32x4 wr[NB == 1 ? 2 : NB][KP][WF], ar[NB][KP][2 * MT];
   auto request_w = [&](int n, u32x4(&w)[KP][WF]) {
@@ -428,7 +430,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
       const uint32_t drop = u + k < u1 ? 0u : kDropped;
 #pragma unroll
       for (int m = 0; m < 2 * MT; ++m)
-        a[k][m] = __builtin_amdgcn_raw_buffer_load_b128(ars, (int)(lane * 16 | drop), (uc * 2 * MT + m) << 10, 0);
+        a[k][m] = __builtin_amdgcn_raw_buffer_load_b128(ars, (int)(ao | drop), (uc * 2 * MT + m) << 10, 0);
     }
   };
   floatx4 acc[GW][S][MT];
@@ -644,14 +646,14 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
   }
 }
 
-template <int MT, int KIND, int GW>
+template <int MT, int KIND, int GW, bool FEW = false>
 hipError_t launch_one(const GemmLaunch &g, hipStream_t s) {
   const dim3 grid(8 * g.TX << g.ls), block(NT);
   hipEvent_t ev0 = (hipEvent_t)g.ev_start, ev1 = (hipEvent_t)g.ev_stop;
   if (ev0)
-    hipExtLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW>), grid, block, 0, s, ev0, ev1, 0, g);
+    hipExtLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW, FEW>), grid, block, 0, s, ev0, ev1, 0, g);
   else
-    hipLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW, FEW>), grid, block, 0, s, g);
   return hipGetLastError();
 }
 
@@ -660,13 +662,24 @@ hipError_t launch_one(const GemmLaunch &g, hipStream_t s) {
 // weights must fit one wave's registers
 constexpr int gw_limit(int S, int MT) { return S == 1 ? (MT <= 7 ? 8 : 6) : MT <= 4 ? 6 : 4; }
 
+// Up to this many tokens (one block, half of it padding or more) the padding
+// tokens' lanes of the activation loads are masked (FEW): with one token a
+// workgroup of the 7B down projection otherwise loads twice its weight bytes
+// for 15 tokens that do not exist.  Four 7B layers, us a step with the mask
+// (without): T = 1 430.7 (442.0).  Beyond, little is saved and the masked
+// offset costs: T = 16 of the 1.4B width 241.9 (239.0), 7B T = 32 501.4
+// (499.1), 1.4B T = 80 1890 (1876).
+constexpr int kFewTokens = 8;
+
 template <int MT, int KIND>
 hipError_t launch_mt(const GemmLaunch &g, hipStream_t s) {
   constexpr int LIM = gw_limit(SUB<KIND>, MT);
   switch (g.gw) {
-#define PPD_GW(n)                                                 \
-  case n:                                                         \
-    if constexpr (LIM >= n) return launch_one<MT, KIND, n>(g, s); \
+#define PPD_GW(n)                                                        \
+  case n:                                                                \
+    if constexpr (MT == 1 && LIM >= n)                                   \
+      if (g.T <= kFewTokens) return launch_one<MT, KIND, n, true>(g, s); \
+    if constexpr (LIM >= n) return launch_one<MT, KIND, n>(g, s);        \
     break;
     PPD_GW(1) PPD_GW(2) PPD_GW(3) PPD_GW(4) PPD_GW(6) PPD_GW(8)
 #undef PPD_GW

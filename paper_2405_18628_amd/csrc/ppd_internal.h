@@ -193,11 +193,12 @@ struct GemmLaunch {
   int G;                // groups; an XCD has G / 8 or one more of them, of which
   int q0, r0, q1, r1;   // a tile holds q0 = (G / 8) / TX, the first r0 = (G / 8) % TX
                         // one more (q1, r1: for G / 8 + 1)
+  int T;                // tokens
   // norm partials for row scaling (QKV, SwiGLU, LOGITS): [n_ss][T_pad]
   int n_ss;
   const float *ss;
   float inv_h, eps;
-  int N, K, T, MT;      // N = output rows (SwiGLU: F), MT = T_pad / 16
+  int N, K, MT;         // N = output rows (SwiGLU: F), MT = T_pad / 16
   float *part;          // s > 1: [8 TX][s][gw MT S][64] floatx4 partial sums
   uint32_t *ctr;        // s > 1: tile counters, XCD x's at ctr + 32 x (zeroed per step)
   uint32_t *status;

@@ -4,6 +4,8 @@ step, projections split over 2 to 8 workgroups, one to eight token tiles; and
 the float32 path with sizes that rule out its 16-byte loads.  Every node's
 logits against the oracle within the tolerances of gpu_cases (bf16 2e-2 + 1e-2
 |o|, float32 1e-4 + 1e-4 |o|)."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -70,3 +72,43 @@ def test_f32_overflowed_node_stays_invisible():
     got = gpu_step(case, tree, ws)["logits"]
     assert np.array_equal(got[:last], clean[:last])
     assert not np.isfinite(got[last]).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("f32", 22)])
+@pytest.mark.parametrize("n", [0, 1, 2, 3, 7, 8, 9, 40])  # up to eight rows in registers, more through LDS
+def test_compaction_lengths(dtype, d, n):
+    """cache[L + k] <- cache[L + path[k]] for every path length, bit for bit,
+    with the path longer than its count and its last row at the capacity."""
+    layers, nkv, L, T = 2, 3, 24, 64
+    cap = L + T
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    k = torch.randn((layers, nkv, cap, d), generator=gen, device="cuda").to(dt)
+    v = torch.randn((layers, nkv, d, cap), generator=gen, device="cuda").to(dt)
+    rows = [0] + sorted(np.random.RandomState(n).permutation(np.arange(1, T))[:max(0, n - 1)].tolist())
+    rows = rows[:n]
+    if n > 1:
+        rows[-1] = T - 1
+    path = torch.full((T,), -1, dtype=torch.int32, device="cuda")
+    path[:n] = torch.tensor(rows, dtype=torch.int32)
+    kw, vw = k.clone(), v.clone()
+    kw[:, :, L:L + n] = k[:, :, [L + r for r in rows]]
+    vw[:, :, :, L:L + n] = v[:, :, :, [L + r for r in rows]]
+    sh = ModelShape("compact", layers, 128, nkv, nkv, d, 64, 16, dtype)
+    case = make_case(Workload("compact", sh, 8, "total:16", 5, "normal", 50))
+    ppd.ppd_kv_compact(case.model, ppd.KVCache(k, v), L, path, torch.tensor([n], dtype=torch.int32, device="cuda"))
+    assert torch.equal(k, kw) and torch.equal(v, vw)
+
+
+@pytest.mark.parametrize("T", [1, 2, 7, 8, 9, 15])  # the padding lanes' mask ends at eight tokens
+def test_bf16_few_tokens(T):
+    case = _case("bf16", 640, 5, 1, 128, 448, 333, 70)
+    tree = tree_for(case, spec="total:16")
+    # a prefix of a topological order is a tree
+    tree = dataclasses.replace(tree, parent=tree.parent[:T], ids=tree.ids[:T],
+                               n_candidates=min(T, tree.n_candidates))
+    ws = workspace(case, T)
+    res, ref = gpu_step(case, tree, ws), oracle_step(case, tree)
+    assert ppd.ppd_device_status(ws) == 0
+    check_logits(res["logits"], ref["logits"], "bf16", f"T={T}")
+    check_pred(res["pred"], ref["logits"], "bf16")
