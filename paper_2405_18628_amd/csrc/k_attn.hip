@@ -19,9 +19,11 @@
 // 1) for one tile (1.4B, T = 16: 9.2 us against 9.8 with (4, 2, 1)), (4, 2, 1)
 // up to four (7B, T = 64: 18.4 us; (2, 4, 2) 20.5), (4, 2, 2) up to eight.
 // The waves' blocks are merged through LDS at the end.  With KS > 1 each
-// query's (O, m, l) is stored and the splits are added in split order inside
-// the kernel: a head's splits share an XCD, so they meet in its L2; each split,
-// once all have arrived at the head's counter, merges its share of the queries.
+// query's (O, m, l) is stored and the splits are added in split order: inside
+// the kernel where an XCD's workgroups are resident together (a head's splits
+// share an XCD, so they meet in its L2; each split, once all have arrived at
+// the head's counter, merges its share of the queries), else -- batches of
+// unequal lengths with more heads than compute units -- by a second launch.
 //
 // Per 32-key block and query tile, on the matrix cores
 // (v_mfma_f32_16x16x32_bf16):
@@ -142,8 +144,9 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnLaunch p) {
   const int lr = lane & 15, lg = lane >> 4;
   // this workgroup's XCD set xs and slot -> sequence, head, split
   const int xs = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int unit = (p.nh + 7) / 8;
   int sq = 0;
-  for (int j = 1; j < p.sb.B; ++j) sq = slot >= p.slot0[j] ? j : sq;
+  for (int j = 1; j < p.sb.B; ++j) sq = (unsigned)(slot - p.slot0[j]) < (unsigned)(unit * p.splits[j]) ? j : sq;
   const int KS = p.splits[sq];
   const int local = slot - p.slot0[sq];
   const int ks = local % KS, hl = local / KS;
@@ -422,7 +425,7 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnLaunch p) {
       if (d4 == 0) *(float2 *)(row + 128) = float2{M, l};
     }
   }
-  if (KS == 1) return;
+  if (KS == 1 || !p.meet) return;
   // every split of the head stores its rows (in this XCD's L2) and arrives at
   // the head's counter; then each merges queries [T ks / KS, T (ks + 1) / KS)
   asm volatile("" ::: "memory");
@@ -444,18 +447,48 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnLaunch p) {
   }
 }
 
+// ---- the second launch where a head's splits do not meet: workgroup
+// (sequence and head, 16-query tile); thread -> query tid / 32, dims 4 (tid %
+// 32) .. + 3
+__global__ __launch_bounds__(NT) void attn_merge_kernel(AttnLaunch p) {
+  const int sq = blockIdx.x / p.nh, h = blockIdx.x % p.nh;
+  const int ql = blockIdx.y * 16 + (threadIdx.x >> 5), d4 = (threadIdx.x & 31) * 4;
+  const int KS = p.splits[sq], t0 = p.sb.t0[sq];
+  if (KS == 1 || ql >= p.sb.t0[sq + 1] - t0) return;  // one split: already final
+  const size_t split_floats = (size_t)p.T_pad * OROW;
+  const float *hp = p.part + (size_t)h * p.max_splits * split_floats + (size_t)(t0 + ql) * OROW;
+  const floatx4 o = merge_splits(KS, [&](int s0, floatx4(&ml)[MERGE_B], floatx4(&r)[MERGE_B]) {
+#pragma unroll
+    for (int v = 0; v < MERGE_B; ++v) {
+      const float *row = hp + (size_t)min(s0 + v, KS - 1) * split_floats;
+      ml[v] = *(const floatx4 *)(row + 128);
+      r[v] = *(const floatx4 *)(row + d4);
+    }
+  });
+  store_plane4(p.out, p.T_pad >> 4, t0 + ql, h * 128 + d4, {o[0], o[1], o[2], o[3]});
+}
+
 }  // namespace
 
 int attn_blocks_per_step(int tiles) { return tiles <= 1 ? 4 : 2; }
 
 hipError_t launch_attn_bf16(const AttnLaunch &a, hipStream_t s) {
-  const dim3 grid(8 * a.slot0[a.sb.B]), block(NT);
+  const dim3 grid(8 * a.n_slots), block(NT);
   auto kernel = a.tiles <= 1   ? attn_bf16_kernel<1, 2, 4>
                 : a.tiles <= 4 ? attn_bf16_kernel<1, 4, 2>
                                : attn_bf16_kernel<2, 4, 2>;
-  if (a.ev_start)
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, (hipEvent_t)a.ev_start, (hipEvent_t)a.ev_stop, 0, a);
+  const bool merge = !a.meet && *std::max_element(a.splits, a.splits + a.sb.B) > 1;
+  const hipEvent_t ev0 = (hipEvent_t)a.ev_start, ev1 = (hipEvent_t)a.ev_stop;
+  if (ev0)
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ev0, merge ? (hipEvent_t) nullptr : ev1, 0, a);
   else
     hipLaunchKernelGGL(kernel, grid, block, 0, s, a);
+  if (merge) {
+    const dim3 mgrid(a.sb.B * a.nh, a.tiles);
+    if (ev1)
+      hipExtLaunchKernelGGL(attn_merge_kernel, mgrid, block, 0, s, (hipEvent_t) nullptr, ev1, 0, a);
+    else
+      hipLaunchKernelGGL(attn_merge_kernel, mgrid, block, 0, s, a);
+  }
   return hipGetLastError();
 }

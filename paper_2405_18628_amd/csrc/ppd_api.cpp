@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <string>
 
 #include "ppd_internal.h"
@@ -207,40 +208,126 @@ constexpr int kSpinLimit = 1 << 14;  // bounded wait of a tile's slices (~10-20 
 // heads and splits on one of the XCD's 32 compute units.
 int attn_max_splits(int nh) { return std::max(1, std::min(PPD_ATTN_MAX_SPLITS, kCUs / nh)); }
 
-// The attention's key splits.  An XCD's heads x splits of all sequences must
-// fit its 32 compute units together, or nothing is split: the slots left are
-// given one by one to the sequence with the most blocks per split, as long as
-// a split keeps kAttnMinBlocks 32-key blocks; then each sequence takes the
-// fewest splits that need no more steps of the kernel.
-constexpr int kAttnMinBlocks = 4;
+// The attention's key splits.  Either the splits of a head meet in the kernel,
+// or a second launch adds them.
+//
+// Meeting needs an XCD's heads x splits of all sequences on its 32 compute
+// units together: the slots left are given one by one to the sequence with the
+// most blocks per split, as long as a split keeps kAttnMinBlocks 32-key blocks.
+// A batch's heads take at most kAttnMeetBatch splits: workgroups start in
+// order, so a launch holds at most one incomplete head an XCD, and two launches
+// of two streams (2 x 15 waiting workgroups) always leave compute units for the
+// ones they wait for.
+//
+// Where that leaves a batch unbalanced (no slot left for a sequence much longer
+// than the others, or a second round of a few workgroups) every sequence is cut
+// into chunks of an even share of all blocks, in one round or two, and a second
+// launch adds the splits.  The cheaper by the time of the last workgroup is
+// taken, each counted as its blocks and kAttnSlotBlocks for what it does
+// besides, the second launch as kAttnMergeBlocks: a block of a 16-token tree
+// takes ~0.33 us, and no less than twice that while all 256 compute units read
+// keys of their own (6.2 TB/s).  us a launch, 16-token trees, meeting (second
+// launch): 7B, eight sequences of 16384 and 7 x 256 tokens 177.7 (75.8), 13B,
+// six of 8192 and 5 x 512 98.0 (52.1), 13B, two of 32768 and 256 113 (123).
+constexpr int kAttnMinBlocks = 4, kAttnMeetBatch = 16, kAttnSlotBlocks = 16, kAttnMergeBlocks = 16;
 
-void plan_attn(AttnLaunch &a, bool xcd_sync) {
-  const int B = a.sb.B, unit = (a.nh + 7) / 8;
-  int nblk[PPD_BATCH_MAX], used = B * unit;
-  a.tiles = 1;
+struct AttnPlan {
+  int splits[PPD_BATCH_MAX], chunk[PPD_BATCH_MAX], order[PPD_BATCH_MAX];  // order: longest chunk first
+  int slots;
+  bool meet;
+};
+
+// chunks and slots of a plan whose splits are wanted so: each sequence takes the
+// fewest splits that need no more steps of the kernel
+void attn_chunks(AttnPlan &p, int B, const int *nblk, int step, int unit) {
+  p.slots = 0;
   for (int j = 0; j < B; ++j) {
-    const int T = a.sb.t0[j + 1] - a.sb.t0[j];
-    a.tiles = std::max(a.tiles, (T + 15) / 16);
-    nblk[j] = (a.sb.L[j] + T + 31) / 32;
-    a.splits[j] = 1;
+    const int per = (nblk[j] + p.splits[j] - 1) / p.splits[j];
+    p.chunk[j] = (per + step - 1) / step * step;
+    p.splits[j] = (nblk[j] + p.chunk[j] - 1) / p.chunk[j];
+    p.slots += unit * p.splits[j];
+    p.order[j] = j;
   }
+  std::stable_sort(p.order, p.order + B, [&](int a, int b) { return p.chunk[a] > p.chunk[b]; });
+}
+
+// when the last of an XCD's workgroups ends, in blocks: each starts, in order,
+// on the compute unit that is free first
+int attn_makespan(const AttnPlan &p, int B, const int *nblk, int unit) {
+  int busy[32] = {0}, end = 0;  // a min-heap
+  for (int i = 0; i < B; ++i) {
+    const int j = p.order[i];
+    const int t = kAttnSlotBlocks + std::min(p.chunk[j], nblk[j]);
+    for (int w = 0; w < unit * p.splits[j]; ++w) {
+      std::pop_heap(busy, busy + 32, std::greater<int>());
+      end = std::max(end, busy[31] += t);
+      std::push_heap(busy, busy + 32, std::greater<int>());
+    }
+  }
+  return end;
+}
+
+AttnPlan plan_attn(int nh, int nkv, int B, const int *nblk, int step, bool xcd_sync) {
+  const int unit = (nh + 7) / 8, max_splits = attn_max_splits(nh);
+  AttnPlan best{};
+  best.meet = true;
+  int used = B * unit, total = 0;
+  for (int j = 0; j < B; ++j) {
+    best.splits[j] = 1;
+    total += unit * nblk[j];
+  }
+  const int cap = B > 1 ? std::min(max_splits, kAttnMeetBatch) : max_splits;
   for (; xcd_sync && used + unit <= 32; used += unit) {
-    int best = -1;
+    int longest = -1;
     for (int j = 0; j < B; ++j)
-      if (nblk[j] >= (a.splits[j] + 1) * kAttnMinBlocks && a.splits[j] < a.max_splits &&
-          (best < 0 || (long)nblk[j] * a.splits[best] > (long)nblk[best] * a.splits[j]))
-        best = j;
-    if (best < 0) break;
-    ++a.splits[best];
+      if (nblk[j] >= (best.splits[j] + 1) * kAttnMinBlocks && best.splits[j] < cap &&
+          (longest < 0 || (long)nblk[j] * best.splits[longest] > (long)nblk[longest] * best.splits[j]))
+        longest = j;
+    if (longest < 0) break;
+    ++best.splits[longest];
   }
-  const int step = attn_blocks_per_step(a.tiles);
-  a.slot0[0] = 0;
+  attn_chunks(best, B, nblk, step, unit);
+  if (B == 1 && xcd_sync) return best;
+  const int stream = (int)(2L * total * nkv / (32 * nh));
+  // (of plans that the stream bounds alike the shorter one)
+  auto cost = [&](int span) { return 8 * std::max(stream, span) + span; };
+  int best_t = cost(attn_makespan(best, B, nblk, unit));
+  for (int rounds = 1; rounds <= 2; ++rounds) {
+    const int share = std::max(kAttnMinBlocks, (total + 32 * rounds - 1) / (32 * rounds));
+    if (cost(share + kAttnSlotBlocks) + 8 * kAttnMergeBlocks >= best_t) continue;
+    AttnPlan p{};
+    for (int j = 0; j < B; ++j) p.splits[j] = std::max(1, std::min(max_splits, (nblk[j] + share - 1) / share));
+    attn_chunks(p, B, nblk, step, unit);
+    const int t = cost(attn_makespan(p, B, nblk, unit)) + 8 * kAttnMergeBlocks;
+    if (t < best_t) best_t = t, best = p;
+  }
+  return best;
+}
+
+// 32-key blocks of the sequences, and the most 16-query tiles one has
+int attn_blocks(int B, const int *L, const int *T, int *nblk) {
+  int tiles = 1;
   for (int j = 0; j < B; ++j) {
-    const int per = (nblk[j] + a.splits[j] - 1) / a.splits[j];
-    a.chunk[j] = (per + step - 1) / step * step;
-    a.splits[j] = (nblk[j] + a.chunk[j] - 1) / a.chunk[j];
-    a.slot0[j + 1] = a.slot0[j] + unit * a.splits[j];
-    a.ctr0[j] = j * unit;  // used only with splits: then all slots fit 32, and so do the counters
+    tiles = std::max(tiles, (T[j] + 15) / 16);
+    nblk[j] = (L[j] + T[j] + 31) / 32;
+  }
+  return tiles;
+}
+
+void set_attn_plan(AttnLaunch &a, const int *L, const int *T, bool xcd_sync) {
+  const int B = a.sb.B, unit = (a.nh + 7) / 8;
+  int nblk[PPD_BATCH_MAX];
+  a.tiles = attn_blocks(B, L, T, nblk);
+  const AttnPlan p = plan_attn(a.nh, a.nkv, B, nblk, attn_blocks_per_step(a.tiles), xcd_sync);
+  a.meet = p.meet;
+  a.n_slots = 0;
+  for (int i = 0; i < B; ++i) {
+    const int j = p.order[i];
+    a.splits[j] = p.splits[j];
+    a.chunk[j] = p.chunk[j];
+    a.slot0[j] = a.n_slots;
+    a.n_slots += unit * p.splits[j];
+    a.ctr0[j] = j * unit;  // used only where splits meet: then all slots fit 32, and so do the counters
   }
 }
 
@@ -271,7 +358,7 @@ WsLayout layout_of(const ppd_model *m, int T) {
   if (bf16) {
     GemmShape gs[5];
     gemm_shapes(m, gs);
-    const bool sync = device_cus() == 256;
+    const bool sync = device_cus() == kCUs;
     for (int mt = 1; mt <= Tp / 16; ++mt)
       for (int i = 0; i < 5; ++i) {
         const GemmPlan p = plan_gemm(gs[i], mt, sync);
@@ -348,7 +435,7 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
   uint32_t *ctr = at<uint32_t>(ws, w.ctr);
   GemmShape gs[5];
   gemm_shapes(m, gs);
-  const bool sync = device_cus() == 256;
+  const bool sync = device_cus() == kCUs;
   GemmPlan plan[5];
   for (int i = 0; i < 5; ++i) plan[i] = plan_gemm(gs[i], MT, sync);
   int launch = 0;  // GEMM launches of this step: counter block `launch`
@@ -391,7 +478,7 @@ ppd_status step_bf16(const ppd_model *m, int B, const ppd_kv *kvs, const int32_t
   a.status = status;
   a.scale_log2 = (float)(1.4426950408889634 / std::sqrt(128.0));
   a.sb = seq_batch(m, B, kvs, Ls, Ts, 0);
-  plan_attn(a, sync);
+  set_attn_plan(a, Ls, Ts, sync);
   uint32_t *attn_ctr = ctr + (size_t)(4 * m->n_layers + 1) * 256;
   const float inv_h = 1.0f / (float)H;
 
@@ -782,6 +869,16 @@ ppd_status ppd_set_kernel_timer(int32_t kind, void *const *start_events, void *c
   g_timer.n = n_events;
   g_timer.next = 0;
   return PPD_OK;
+}
+
+void ppd_plan_attention(int32_t nh, int32_t nkv, int32_t B, const int32_t *L, const int32_t *T, int32_t cus,
+                        int32_t *splits, int32_t *chunk, int32_t info[2]) {
+  int nblk[PPD_BATCH_MAX];
+  const int tiles = attn_blocks(B, L, T, nblk);
+  const AttnPlan p = plan_attn(nh, nkv, B, nblk, attn_blocks_per_step(tiles), cus == kCUs);
+  std::copy(p.splits, p.splits + B, splits);
+  std::copy(p.chunk, p.chunk + B, chunk);
+  info[0] = p.slots, info[1] = p.meet;
 }
 
 const char *ppd_last_error(void) { return g_err.c_str(); }

@@ -19,6 +19,7 @@ from gpu_cases import LazyCache, check_logits, check_pred, make_case, say, tree_
 from synth import workload
 from synth.model import empty_kv, fill_kv_normal
 from synth.trees import Tree, make_tree
+from test_plans_cpu import attention_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -161,3 +162,35 @@ def test_batch_full_width_7b_layer():
                    vb, s["v"][:, :, :, s["L"]:s["L"] + T], f"sequence {j}")
         assert torch.isfinite(ls).all()
         t0 += T
+
+
+@pytest.mark.parametrize("name,Ls,Ts", [
+    ("wide", [1900] + [40] * 7, [16] * 8),                  # 32 heads: one sequence in 8 splits, the rest whole
+    ("wide", [8000, 900, 700, 500, 300, 5, 0], [18] * 7),    # two query tiles each
+    ("wide-gqa", [3000, 700, 33, 0, 1], [25] * 5),          # 64 heads over 8 kv heads, odd prefixes
+    ("wide-gqa", [2999, 70, 33, 0, 1], [90, 8, 9, 8, 8]),   # the long one with a tree over 64 nodes
+])
+def test_ragged_batch_splits_added_by_a_second_launch(name, Ls, Ts):
+    """Batches whose splits do not fit an XCD's compute units together."""
+    case = make_case(workload(name), L=64)
+    seqs = _sequences(case, Ls, [f"total:{T}" for T in Ts], 7700 + len(Ls))
+    say(f"[ragged batch] {name} L={Ls} T={[s['tree'].T for s in seqs]}")
+    splits, _, _, meet = attention_plan(case.shape.n_heads, case.shape.n_kv_heads, Ls,
+                                        [s["tree"].T for s in seqs])
+    assert max(splits) > 1 and not meet
+    trees, parts, logits, pred, ws = _run_batch(case, seqs)
+    assert ppd.ppd_device_status(ws) == 0
+    t0 = 0
+    for j, s in enumerate(seqs):
+        n = s["tree"].T
+        kb = s["k"][:, :, s["L"]:s["L"] + n].clone()
+        vb = s["v"][:, :, :, s["L"]:s["L"] + n].clone()
+        ls, ps = _run_single(case, s)
+        _same_step(logits[t0:t0 + n], ls, pred[t0:t0 + n], ps, kb, s["k"][:, :, s["L"]:s["L"] + n],
+                   vb, s["v"][:, :, :, s["L"]:s["L"] + n], f"sequence {j}")
+        if j < 2:
+            ref = O.verify_forward(case.oracle_model, LazyCache(s["k"], False, s["L"]),
+                                   LazyCache(s["v"], True, s["L"]), s["L"], s["tree"].ids,
+                                   s["tree"].parent, case.shape.dtype)
+            check_logits(logits[t0:t0 + n].cpu().numpy().astype(np.float64), ref["logits"], case.shape.dtype)
+        t0 += n
