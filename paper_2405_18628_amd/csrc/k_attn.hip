@@ -129,7 +129,8 @@ __device__ __forceinline__ floatx4 merge_splits(int KS, ROWS rows) {
   return acc * (1.f / lsum);
 }
 
-template <int NQ, int QW, int PARS>
+// MEET: the splits meet in the kernel (slots in sequence order)
+template <int NQ, int QW, int PARS, bool MEET>
 __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnLaunch p) {
   static_assert(QW * PARS * 64 == NT, "one block and tile set per wave");
   constexpr int kRows = PARS * QW * NQ * 16 * OROW * 4;  // bytes of the waves' rows
@@ -144,9 +145,13 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnLaunch p) {
   const int lr = lane & 15, lg = lane >> 4;
   // this workgroup's XCD set xs and slot -> sequence, head, split
   const int xs = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int unit = (p.nh + 7) / 8;
   int sq = 0;
-  for (int j = 1; j < p.sb.B; ++j) sq = (unsigned)(slot - p.slot0[j]) < (unsigned)(unit * p.splits[j]) ? j : sq;
+  if constexpr (MEET) {
+    for (int j = 1; j < p.sb.B; ++j) sq = slot >= p.slot0[j] ? j : sq;
+  } else {
+    const int unit = (p.nh + 7) / 8;
+    for (int j = 1; j < p.sb.B; ++j) sq = (unsigned)(slot - p.slot0[j]) < (unsigned)(unit * p.splits[j]) ? j : sq;
+  }
   const int KS = p.splits[sq];
   const int local = slot - p.slot0[sq];
   const int ks = local % KS, hl = local / KS;
@@ -425,7 +430,7 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnLaunch p) {
       if (d4 == 0) *(float2 *)(row + 128) = float2{M, l};
     }
   }
-  if (KS == 1 || !p.meet) return;
+  if (!MEET || KS == 1) return;
   // every split of the head stores its rows (in this XCD's L2) and arrives at
   // the head's counter; then each merges queries [T ks / KS, T (ks + 1) / KS)
   asm volatile("" ::: "memory");
@@ -474,9 +479,9 @@ int attn_blocks_per_step(int tiles) { return tiles <= 1 ? 4 : 2; }
 
 hipError_t launch_attn_bf16(const AttnLaunch &a, hipStream_t s) {
   const dim3 grid(8 * a.n_slots), block(NT);
-  auto kernel = a.tiles <= 1   ? attn_bf16_kernel<1, 2, 4>
-                : a.tiles <= 4 ? attn_bf16_kernel<1, 4, 2>
-                               : attn_bf16_kernel<2, 4, 2>;
+  auto kernel = a.tiles <= 1   ? (a.meet ? attn_bf16_kernel<1, 2, 4, true> : attn_bf16_kernel<1, 2, 4, false>)
+                : a.tiles <= 4 ? (a.meet ? attn_bf16_kernel<1, 4, 2, true> : attn_bf16_kernel<1, 4, 2, false>)
+                               : (a.meet ? attn_bf16_kernel<2, 4, 2, true> : attn_bf16_kernel<2, 4, 2, false>);
   const bool merge = !a.meet && *std::max_element(a.splits, a.splits + a.sb.B) > 1;
   const hipEvent_t ev0 = (hipEvent_t)a.ev_start, ev1 = (hipEvent_t)a.ev_stop;
   if (ev0)

@@ -288,6 +288,7 @@ AttnPlan plan_attn(int nh, int nkv, int B, const int *nblk, int step, bool xcd_s
   }
   attn_chunks(best, B, nblk, step, unit);
   if (B == 1 && xcd_sync) return best;
+  best.meet = xcd_sync && best.slots <= 32;  // else nothing is split so far
   const int stream = (int)(2L * total * nkv / (32 * nh));
   // (of plans that the stream bounds alike the shorter one)
   auto cost = [&](int span) { return 8 * std::max(stream, span) + span; };
@@ -322,7 +323,7 @@ void set_attn_plan(AttnLaunch &a, const int *L, const int *T, bool xcd_sync) {
   a.meet = p.meet;
   a.n_slots = 0;
   for (int i = 0; i < B; ++i) {
-    const int j = p.order[i];
+    const int j = p.meet ? i : p.order[i];
     a.splits[j] = p.splits[j];
     a.chunk[j] = p.chunk[j];
     a.slot0[j] = a.n_slots;

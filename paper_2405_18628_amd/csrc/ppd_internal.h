@@ -243,11 +243,11 @@ struct AttnLaunch {
   SeqBatch sb;
   // Workgroup b: XCD set x = b % 8 (heads [nh x / 8, nh (x + 1) / 8)), slot
   // b / 8; sequence s takes the slots from slot0[s] on: ceil(nh / 8) heads x
-  // splits[s], a split holding chunk[s] 32-key blocks; the sequences with the
-  // longest splits come first.  meet: a head's splits meet in the kernel, at
-  // counter ctr + 32 x + ctr0[s] + local head (zeroed per step), which needs all
-  // slots of an XCD on its 32 compute units together (they wait for each
-  // other); else a second launch adds the splits.
+  // splits[s], a split holding chunk[s] 32-key blocks.  meet: a head's splits
+  // meet in the kernel, at counter ctr + 32 x + ctr0[s] + local head (zeroed per
+  // step); all slots of an XCD are on its 32 compute units together (they wait
+  // for each other), in sequence order.  Else the sequences with the longest
+  // splits come first and a second launch adds the splits, if any.
   int slot0[PPD_BATCH_MAX], splits[PPD_BATCH_MAX], chunk[PPD_BATCH_MAX], ctr0[PPD_BATCH_MAX];
   int n_slots, meet;
   uint32_t *ctr;
@@ -280,7 +280,7 @@ hipError_t launch_next_tree(const NextTreeLaunch &p, int n_depths, hipStream_t s
 // The attention's key splits as a step takes them on a device of `cus` compute
 // units, for the tests: splits[s] and chunk[s] (in 32-key blocks) of a batch's
 // sequences with L[s] cached and T[s] tree tokens, info = {slots an XCD's
-// compute units share, 1 where the splits meet in the kernel}.  Host only.
+// compute units share, 1 where splits, if any, meet in the kernel}.  Host only.
 extern "C" void ppd_plan_attention(int32_t nh, int32_t nkv, int32_t B, const int32_t *L, const int32_t *T,
                                    int32_t cus, int32_t *splits, int32_t *chunk, int32_t info[2]);
 

@@ -65,4 +65,5 @@ def test_a_long_sequence_of_a_batch_is_shared(nh, nkv, Ls, T):
     (40, 40, [32768, 256], [16, 16]),  # bound by the cache's stream: nothing to balance
 ])
 def test_even_batches_need_no_second_launch(nh, nkv, Ls, Ts):
-    assert attention_plan(nh, nkv, Ls, Ts)[3]
+    splits, _, _, meet = attention_plan(nh, nkv, Ls, Ts)
+    assert meet or max(splits) == 1
