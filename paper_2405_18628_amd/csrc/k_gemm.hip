@@ -331,7 +331,8 @@ constexpr int slab_bufs(int MT, int WF) {
 // ---- the GEMM.  Workgroup b: XCD x = b % 8, slot j = b / 8 -> tile
 // t = j / s (groups [ga, gb) of the XCD's range, at most GW), K slice
 // ks = j % s (k-steps [u0, u1)).
-template <int MT, int KIND, int GW, bool FEW>
+// TWO: the tile comes in two slices, each keeping the sums it finishes in LDS.
+template <int MT, int KIND, int GW, bool FEW, bool TWO>
 __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
   constexpr int T_pad = MT * 16;
   constexpr int S = SUB<KIND>, WF = GW * S;
@@ -346,6 +347,8 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
   __shared__ float rs_s[T_pad];
   constexpr bool kRows = KIND == GEMM_LOGITS || KIND == GEMM_RESID;  // reductions over the tile's rows
   __shared__ float2 item_s[kRows ? GW * MT * 16 : 1];
+  // TWO: the sums of the items this slice finishes
+  __shared__ __attribute__((aligned(16))) float own_s[TWO ? (GW * MT + 1) / 2 * S * 256 : 4];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -514,8 +517,9 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
   // the tile's slices have met at the counter, slice idx % s (of the whole
   // tile's items) adds the s sums in slice order and finishes the item.  Partial sums: [tile][slice][item][q][lane] floatx4.
   [[maybe_unused]] TokenSlot slot;
+  // (TWO: one sum an item, the slice's that does not finish it: [tile][item][q][lane])
   constexpr int kPart = GW * MT * S * 256;  // floats per workgroup
-  float *part = g.part + ((size_t)gt * s + ks) * kPart;
+  float *part = g.part + (TWO ? (size_t)gt : (size_t)gt * s + ks) * kPart;
 #pragma unroll
   for (int m0 = 0; m0 < MT; m0 += MR) {
     if (m0 > 0) __syncthreads();
@@ -568,15 +572,19 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
         if (idx >= ITEMS || i >= ng || m >= MT) continue;
         floatx4 a[S];
         sum_item(idx, a);
+        float *dst = part + (size_t)(i * MT + m) * S * 256;
+        if constexpr (TWO)
+          if (((i * MT + m) & 1) == ks) dst = own_s + ((i * MT + m) >> 1) * S * 256;
 #pragma unroll
-        for (int q = 0; q < S; ++q)
-          *(floatx4 *)(part + ((size_t)(i * MT + m) * S + q) * 256 + lane * 4) = a[q];
+        for (int q = 0; q < S; ++q) *(floatx4 *)(dst + q * 256 + lane * 4) = a[q];
       }
   }
   if (s > 1) {
-    // this slice's items, dealt to its waves in turn: the s partial sums (its
-    // own too: the same bytes) are added in slice order; the next item's are
-    // requested while this one is finished
+    // this slice's items, dealt to its waves in turn: the s partial sums are
+    // added in slice order; the next item's are requested while this one is
+    // finished.  Its own sums make the round trip with the others' (one code
+    // for every s: where s is 4 or 8 that costs nothing measurable), except
+    // with TWO
     const int nb = (ng + R - 1) / R;  // groups of a class (m, i % R)
     const int n_own = kRows ? ((MT * R - ks + s - 1) >> ls) * nb : (ng * MT - ks + s - 1) >> ls;
     auto item_at = [&](int n, int &i, int &m) {
@@ -591,14 +599,16 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
       return i < ng;
     };
     EpiIn<KIND> in[2];
-    floatx4 buf[2][8][S];
-    const __amdgpu_buffer_rsrc_t rp = rsrc_of(g.part + (size_t)gt * s * kPart, (uint32_t)s * kPart * 4);
-    auto ask_sums = [&](int n, floatx4(&d)[8][S]) {
+    constexpr int NP = TWO ? 1 : 8;  // sums that come from L2 (TWO: the other slice's)
+    floatx4 buf[2][NP][S];
+    const __amdgpu_buffer_rsrc_t rp = rsrc_of(g.part + (size_t)gt * (TWO ? 1 : s) * kPart,
+                                               (uint32_t)(TWO ? 1 : s) * kPart * 4);
+    auto ask_sums = [&](int n, floatx4(&d)[NP][S]) {
       int i, m;
       const uint32_t drop = n < n_own && item_at(n, i, m) ? 0u : kDropped;
       if (drop) i = m = 0;
 #pragma unroll
-      for (int sl = 0; sl < 8; ++sl)
+      for (int sl = 0; sl < NP; ++sl)
 #pragma unroll
         for (int q = 0; q < S; ++q)  // past the last slice: beyond the resource, zeros
           d[sl][q] = load_l2(rp, (uint32_t)(sl * kPart * 4 + ((i * MT + m) * S + q) * 1024 + lane * 16) | drop);
@@ -607,15 +617,16 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
       int i, m;
       if (n < n_own && item_at(n, i, m)) epi_load<KIND>(g, ga + i, m, e);
     };
-    auto finish = [&](int n, const floatx4(&d)[8][S], const EpiIn<KIND> &e) {
+    auto finish = [&](int n, const floatx4(&d)[NP][S], const EpiIn<KIND> &e) {
       int i, m;
       if (n >= n_own || !item_at(n, i, m)) return;
       floatx4 a[S];
 #pragma unroll
       for (int q = 0; q < S; ++q) {
         a[q] = d[0][q];
+        if constexpr (TWO) a[q] += *(const floatx4 *)(own_s + (n * S + q) * 256 + lane * 4);
 #pragma unroll
-        for (int sl = 1; sl < 8; ++sl) a[q] += d[sl][q];
+        for (int sl = 1; sl < NP; ++sl) a[q] += d[sl][q];
       }
       if constexpr (KIND == GEMM_QKV) find_slot(g, m, slot);
       epilogue<KIND>(g, ga + i, m, a, rs_s, e, item_s + (kRows ? (i * MT + m) * 16 : 0), slot);
@@ -646,14 +657,14 @@ __global__ __launch_bounds__(NT, 1) void gemm_bf16_kernel(GemmLaunch g) {
   }
 }
 
-template <int MT, int KIND, int GW, bool FEW = false>
+template <int MT, int KIND, int GW, bool FEW = false, bool TWO = false>
 hipError_t launch_one(const GemmLaunch &g, hipStream_t s) {
   const dim3 grid(8 * g.TX << g.ls), block(NT);
   hipEvent_t ev0 = (hipEvent_t)g.ev_start, ev1 = (hipEvent_t)g.ev_stop;
   if (ev0)
-    hipExtLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW, FEW>), grid, block, 0, s, ev0, ev1, 0, g);
+    hipExtLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW, FEW, TWO>), grid, block, 0, s, ev0, ev1, 0, g);
   else
-    hipLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW, FEW>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((gemm_bf16_kernel<MT, KIND, GW, FEW, TWO>), grid, block, 0, s, g);
   return hipGetLastError();
 }
 
@@ -661,6 +672,18 @@ hipError_t launch_one(const GemmLaunch &g, hipStream_t s) {
 // accumulators (4 GW S MT registers), a step's activations and two steps'
 // weights must fit one wave's registers
 constexpr int gw_limit(int S, int MT) { return S == 1 ? (MT <= 7 ? 8 : 6) : MT <= 4 ? 6 : 4; }
+
+// Tiles of seven groups or more in two slices (TWO): QKV with two to seven token
+// blocks, gate/up with four.  The sums a slice finishes stay in its LDS; with
+// all of them on the round trip through L2, and six dropped loads an item, two
+// slices were not worth it.  13B, T = 56, us a launch whole, in two slices, so:
+// QKV 42.1, 40.5, 39.7; gate/up 59.5, 59.2, 57.9; a step of 40 layers 7450 ->
+// 7240.  Not for smaller tiles (7B, T = 96, QKV: 0.5 us a layer lost) nor
+// gate/up with three token blocks (4608 and 5120 columns: 0.6 to 1 % of a step
+// lost).
+constexpr int two_slice_gw(int kind, int MT) {
+  return kind == GEMM_QKV && MT >= 2 && MT <= 7 ? 8 : kind == GEMM_SWIGLU && MT == 4 ? 7 : 0;
+}
 
 // Up to this many tokens (one block, half of it padding or more) the padding
 // tokens' lanes of the activation loads are masked (FEW): with one token a
@@ -673,7 +696,9 @@ constexpr int kFewTokens = 8;
 
 template <int MT, int KIND>
 hipError_t launch_mt(const GemmLaunch &g, hipStream_t s) {
-  constexpr int LIM = gw_limit(SUB<KIND>, MT);
+  constexpr int LIM = gw_limit(SUB<KIND>, MT), TGW = two_slice_gw(KIND, MT);
+  if constexpr (TGW > 0)
+    if (g.gw == TGW && g.ls == 1) return launch_one<MT, KIND, TGW, false, true>(g, s);
   switch (g.gw) {
 #define PPD_GW(n)                                                        \
   case n:                                                                \
@@ -746,6 +771,7 @@ int gemm_groups_of(int kind, int N) {
 int gemm_sub_of(int kind) { return kind == GEMM_SWIGLU ? 2 : 1; }
 
 int gemm_gw_max(int kind, int MT) { return gw_limit(gemm_sub_of(kind), MT); }
+int gemm_two_slice_gw(int kind, int MT) { return two_slice_gw(kind, MT); }
 
 hipError_t launch_pack_weight(int kind, int N, int K, const bf16_t *src, bf16_t *dst, hipStream_t s) {
   if (K % KC) return hipErrorInvalidValue;

@@ -146,18 +146,25 @@ struct GemmShape {
 // unit can have outstanding) and its activation bytes, L2 hits, ~110 GB/s on
 // top of that, and all weights together stream at 6.2 TB/s at most.  s > 1
 // divides the activation bytes by s and adds the exchange of the partial
-// sums: ~2 us of latency and ~4 GB/s for a workgroup's sums.  Compared with
-// every plan that fits, timed one by one (1.4B, 7B, 13B and GQA shapes, T = 1
-// .. 128), the choice is the fastest or within 1.3 us of it.  E.g. 7B, T = 64:
-// QKV and gate/up whole (30.3, 43.1 us; in 2 slices 34.2, 52.2), output
-// projection in 4 slices (18.7 us; 20.0 whole, 22.6 in 8), down projection in
-// 4 (32.1; 46.8 whole, 33.4 in 8); T = 16: output projection whole (12.0 us;
-// 13.7 in 4 slices).
+// sums: ~2 us of latency and ~4 GB/s for a workgroup's sums; two slices of a
+// tile of seven groups or more, whose own sums stay in LDS, 2.5 us and ~13.5
+// GB/s, part of it while the stream still runs.
+// Compared with every plan that fits, the steps timed with one GEMM changed at
+// a time (270 (shape, kind, T) of the 1.4B, 7B, 13B, GQA and two narrower
+// widths, T = 1 .. 128), the choice is the fastest or within 2 us of it in all
+// but a dozen: projections 2560 or 1024 wide with T = 48 .. 96 run whole and
+// would gain up to 5 us in 4 slices.
 struct GemmPlan {
   int gw = 1, TX = 32, s = 1;
   // rows of the tiles' reductions (sums of squares, argmax)
   int rows(int MT) const { return 8 * TX * ((s + MT - 1) / MT); }
 };
+
+// Columns from which the cheaper exchange of two slices is counted on (us a step
+// of three layers, whole tiles -> two slices, T = 64 and 96: 3072 columns 380.7 ->
+// 385.5, 467.9 -> 476.4; 4096 475.9 -> 475.3, 574.5 -> 578.0; 4608 494.6 -> 492.9,
+// 610.2 -> 607.2; 5120 538.5 -> 532.5, 660.7 -> 653.5).
+constexpr int kTwoSliceK = 4608;
 
 GemmPlan plan_gemm(const GemmShape &sh, int MT, bool xcd_sync) {
   GemmPlan best;
@@ -171,11 +178,17 @@ GemmPlan plan_gemm(const GemmShape &sh, int MT, bool xcd_sync) {
     int TX = 32 / s, h = std::max(1, (nx + TX - 1) / TX);
     if (s == 1)
       for (; h > gmax; h = (nx + TX - 1) / TX) TX += 32;
-    const int gw = h == 5 ? 6 : h == 7 ? 8 : h;
-    if (gw > gmax) continue;
+    // a tile of seven groups or more in two slices has a cheaper exchange
+    const int two_gw = s == 2 && sh.K >= kTwoSliceK ? gemm_two_slice_gw(sh.kind, MT) : 0;
+    const bool two = h >= 7 && h <= two_gw;
+    const int gw = two ? two_gw : h == 5 ? 6 : h == 7 ? 8 : h;
+    if (gw > gmax && !two) continue;
     const double cols = (double)((kc + s - 1) / s) * 64;
     const double wb = 2.0 * h * 16 * S * cols, ab = 4.0 * MT * 16 * cols, pb = 1024.0 * h * S * MT;
-    const double t = std::max((TX + 31) / 32 * (wb / 36e9 + ab / 110e9), hbm) + (s > 1 ? 2e-6 + pb / 4e9 : 0.0);
+    const double load = (TX + 31) / 32 * (wb / 36e9 + ab / 110e9);
+    const double t = two     ? std::max(load + 2.5e-6 + pb / 13.5e9, hbm + 2e-6)
+                     : s > 1 ? std::max(load, hbm) + 2e-6 + pb / 4e9
+                             : std::max(load, hbm);
     if (t < best_t) {
       best_t = t;
       best.gw = gw;
@@ -199,7 +212,8 @@ void gemm_shapes(const ppd_model *m, GemmShape out[5]) {
 // bytes of the partial sums of a plan (0 when every tile is whole)
 size_t plan_part_bytes(const GemmShape &sh, const GemmPlan &p, int MT) {
   if (p.s == 1) return 0;
-  return (size_t)8 * p.TX * p.s * p.gw * gemm_sub_of(sh.kind) * MT * 64 * 16;
+  const bool two = p.s == 2 && p.gw == gemm_two_slice_gw(sh.kind, MT);
+  return (size_t)8 * p.TX * (two ? 1 : p.s) * p.gw * gemm_sub_of(sh.kind) * MT * 64 * 16;
 }
 
 constexpr int kSpinLimit = 1 << 14;  // bounded wait of a tile's slices (~10-20 ms)
@@ -870,6 +884,11 @@ ppd_status ppd_set_kernel_timer(int32_t kind, void *const *start_events, void *c
   g_timer.n = n_events;
   g_timer.next = 0;
   return PPD_OK;
+}
+
+void ppd_plan_gemm(int32_t kind, int32_t N, int32_t K, int32_t T, int32_t cus, int32_t plan[3]) {
+  const GemmPlan p = plan_gemm({kind, N, K}, t_pad_of(T) / 16, cus == kCUs);
+  plan[0] = p.gw, plan[1] = p.TX, plan[2] = p.s;
 }
 
 void ppd_plan_attention(int32_t nh, int32_t nkv, int32_t B, const int32_t *L, const int32_t *T, int32_t cus,

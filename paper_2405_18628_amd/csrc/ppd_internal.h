@@ -199,7 +199,7 @@ struct GemmLaunch {
   const float *ss;
   float inv_h, eps;
   int N, K, MT;         // N = output rows (SwiGLU: F), MT = T_pad / 16
-  float *part;          // s > 1: [8 TX][s][gw MT S][64] floatx4 partial sums
+  float *part;          // s > 1: [8 TX][s][gw MT S][64] floatx4 partial sums (gemm_two_slice_gw tiles: no [s])
   uint32_t *ctr;        // s > 1: tile counters, XCD x's at ctr + 32 x (zeroed per step)
   uint32_t *status;
   int spin_limit;       // bounded wait for a tile's other slices
@@ -228,6 +228,7 @@ enum GemmKind { GEMM_QKV = 0, GEMM_RESID = 1, GEMM_SWIGLU = 2, GEMM_LOGITS = 3 }
 int gemm_groups_of(int kind, int N);  // groups of a GEMM with N output rows (gate/up: features)
 int gemm_sub_of(int kind);            // 16-row sub-tiles per group (2 for gate/up)
 int gemm_gw_max(int kind, int MT);    // largest tile (in groups) instantiated for MT token tiles
+int gemm_two_slice_gw(int kind, int MT);  // tile (seven groups or more) with an exchange of its own in two slices, or 0
 hipError_t launch_pack_weight(int kind, int N, int K, const bf16_t *src, bf16_t *dst, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmLaunch &g, hipStream_t s);
 
@@ -277,10 +278,15 @@ struct NextTreeLaunch {
 };
 hipError_t launch_next_tree(const NextTreeLaunch &p, int n_depths, hipStream_t s);
 
-// The attention's key splits as a step takes them on a device of `cus` compute
-// units, for the tests: splits[s] and chunk[s] (in 32-key blocks) of a batch's
-// sequences with L[s] cached and T[s] tree tokens, info = {slots an XCD's
-// compute units share, 1 where splits, if any, meet in the kernel}.  Host only.
+// The partition a step of T tokens takes for a GEMM of GemmKind `kind` (N output
+// rows, gate/up: features; K columns) on a device of `cus` compute units, for
+// the tests that must reach a given one: plan = {groups of the largest tile,
+// tiles per XCD, K slices}.  Host only.
+extern "C" void ppd_plan_gemm(int32_t kind, int32_t N, int32_t K, int32_t T, int32_t cus, int32_t plan[3]);
+
+// The same for the attention: splits[s] and chunk[s] (in 32-key blocks) of a
+// batch's sequences with L[s] cached and T[s] tree tokens, info = {slots an
+// XCD's compute units share, 1 where splits, if any, meet in the kernel}.
 extern "C" void ppd_plan_attention(int32_t nh, int32_t nkv, int32_t B, const int32_t *L, const int32_t *T,
                                    int32_t cus, int32_t *splits, int32_t *chunk, int32_t info[2]);
 
