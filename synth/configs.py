@@ -78,15 +78,14 @@ VICUNA_13B = ModelShape("vicuna-13b", 40, 5120, 40, 40, 128, 13824, 32000, "bf16
 SMALL_BF16 = ModelShape("small-bf16", 2, 512, 4, 4, 128, 1344, 1000, "bf16")
 SMALL_GQA = ModelShape("small-gqa-bf16", 2, 512, 4, 2, 128, 1408, 1000, "bf16")
 # narrow hidden, 7B-wide heads and ffn: the QKV and gate/up GEMMs take the
-# 7B tilings (256 QKV tiles of 3 row groups; 230 gate/up tiles of 48
-# features, the last one ragged) at a size the oracle runs in seconds
+# 7B tilings (256 QKV tiles of 3 groups; 256 gate/up tiles of 2 or 3 groups of
+# 16 features) at a size the oracle runs in seconds
 WIDE_BF16 = ModelShape("wide-bf16", 1, 512, 32, 32, 128, 11008, 1000, "bf16")
 # narrow hidden, 1.4B-wide heads and ffn: QKV and gate/up take the 1.4B
-# tilings (split QKV; 176 gate/up tiles of 2 feature groups, each group's
-# two k-steps on two waves)
+# tilings (whole tiles of up to 2 groups)
 MID_BF16 = ModelShape("mid-bf16", 1, 512, 16, 16, 128, 5632, 1000, "bf16")
-# grouped-query heads whose QKV groups (80 x 8 = 640) leave the last 3-group
-# QKV tile with one real group
+# grouped-query heads whose QKV groups (640, 80 an XCD) deal unevenly: tiles of
+# 2 and 3
 WIDE_GQA = ModelShape("wide-gqa-bf16", 1, 512, 64, 8, 128, 1344, 1000, "bf16")
 
 WORKLOADS = {

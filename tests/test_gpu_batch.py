@@ -17,9 +17,10 @@ import oracle as O
 import paper_2405_18628_amd as ppd
 from gpu_cases import LazyCache, check_logits, check_pred, make_case, say, tree_tensors
 from synth import workload
+from synth.configs import ModelShape, Workload
 from synth.model import empty_kv, fill_kv_normal
 from synth.trees import Tree, make_tree
-from test_plans_cpu import attention_plan
+from test_plans_cpu import attention_plan, gemm_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -194,3 +195,22 @@ def test_ragged_batch_splits_added_by_a_second_launch(name, Ls, Ts):
                                    s["tree"].parent, case.shape.dtype)
             check_logits(logits[t0:t0 + n].cpu().numpy().astype(np.float64), ref["logits"], case.shape.dtype)
         t0 += n
+
+
+def test_batch_with_split_qkv():
+    """QKV in two K slices (32 heads over 8 kv heads, 4096 wide): each sequence's
+    keys and values are stored after the exchange."""
+    sh = ModelShape("gqa-layer", 1, 4096, 32, 8, 128, 1024, 500, "bf16")
+    case = make_case(Workload("gqa-layer", sh, 64, "total:16", 5, "normal", 51))
+    Ls = [300, 0, 77]
+    seqs = _sequences(case, Ls, ["total:20", "total:9", "total:30"], 7900)
+    assert gemm_plan("qkv", 4096, 32, 8, 1024, 500, 59)[2] == 2
+    trees, parts, logits, pred, ws = _run_batch(case, seqs)
+    assert ppd.ppd_device_status(ws) == 0
+    t0 = 0
+    for j, s in enumerate(seqs):
+        T = s["tree"].T
+        ref = O.verify_forward(case.oracle_model, LazyCache(s["k"], False, s["L"]), LazyCache(s["v"], True, s["L"]),
+                               s["L"], s["tree"].ids, s["tree"].parent, sh.dtype)
+        check_logits(logits[t0:t0 + T].cpu().numpy().astype(np.float64), ref["logits"], sh.dtype)
+        t0 += T

@@ -13,6 +13,7 @@ import torch
 import paper_2405_18628_amd as ppd
 from gpu_cases import check_logits, check_pred, gpu_step, make_case, oracle_step, tree_for, workspace
 from synth.configs import ModelShape, Workload
+from test_plans_cpu import SPLIT_CASES
 
 pytestmark = pytest.mark.gpu
 
@@ -34,8 +35,8 @@ def _check(case, spec):
 @pytest.mark.parametrize("shape", [
     (128, 1, 1, 64, 7),        # 4 gate/up groups and 1 LM-head group for 8 XCDs
     (640, 5, 1, 448, 333),     # 10 and 7 chunks of columns, ragged groups
-    (384, 8, 2, 1152, 1000),   # 18 chunks: slices of 2 and 3
-    (2048, 16, 16, 5632, 500),  # the 1.4B widths: output / down split 2, 4, 8 ways
+    (384, 8, 2, 1152, 1000),   # 18 chunks of columns, ragged groups
+    (2048, 16, 16, 5632, 500),  # the 1.4B widths: output / down whole or in 4 slices, LM head in 8
 ])
 @pytest.mark.parametrize("specs", [("chain:1", "total:33", "total:80"), ("total:16", "total:50", "total:128")])
 def test_bf16_tilings(shape, specs):
@@ -43,6 +44,15 @@ def test_bf16_tilings(shape, specs):
     case = _case("bf16", hidden, heads, kv, 128, ffn, vocab, 70, layers=1 if hidden > 1000 else 2)
     for spec in specs:
         _check(case, spec)
+
+
+@pytest.mark.parametrize("shape,T,plans", SPLIT_CASES)
+def test_bf16_split_tiles(shape, T, plans):
+    """GEMMs of every kind in 2, 4 and 8 K slices (that they are is checked
+    beside SPLIT_CASES)."""
+    hidden, heads, kv, ffn, vocab = shape
+    case = _case("bf16", hidden, heads, kv, 128, ffn, vocab, 70, layers=1)
+    _check(case, f"total:{T}")
 
 
 @pytest.mark.parametrize("hidden,heads,kv,d,ffn,vocab,L,cap,spec", [
