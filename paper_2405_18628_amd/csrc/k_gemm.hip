@@ -319,7 +319,11 @@ constexpr uint32_t kDropped = 0x80000000u;
 // 613 / 579 / 543 / 481, activations in one buffer and weights in two of 4 to
 // 8 steps 642 / 605 / 546 / 479.
 constexpr int buf_steps(int MT, int WF) {
-  return std::min(440 - 4 * WF * MT, 4 * 66) / (4 * (WF + 2 * MT));
+  // twelve weight fragments a step or more: ten registers of addresses more
+  // (gate/up tiles of 6 groups with four token blocks spilled 12 bytes a lane
+  // and took 28.3 us a launch at 4096 x 4288, 65.6 at 4096 x 20480, T = 64; now
+  // 26.8 and 61.9)
+  return std::min((WF < 12 ? 440 : 430) - 4 * WF * MT, 4 * 66) / (4 * (WF + 2 * MT));
 }
 constexpr int slab_steps(int MT, int WF) {
   return std::max(1, std::min({(MT == 1 ? 16 : 8) / (2 * MT), buf_steps(MT, WF) / 3}));
