@@ -232,14 +232,30 @@ __global__ __launch_bounds__(64 * kAttnWaves) void f32_attention_kernel(
   const int n_keys = L + T;
   for (int k0 = 16 * wave; k0 < n_keys; k0 += 16 * kAttnWaves) {
     const float *kr = kb + (size_t)min(k0 + lr, n_keys - 1) * d;
-    floatx4 kv[ND], vv[ND];
+    // single-element key loads are used as they come: all of a wide head's, and
+    // their addresses, do not fit the registers beside the values
+    constexpr bool kAhead = VK || ND < 8;
+    floatx4 kv[kAhead ? ND : 1], vv[ND];
+    floatx4 s = floatx4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (kAhead) {
 #pragma unroll
-    for (int j = 0; j < ND; ++j) kv[j] = load4<VK>(kr, 16 * j + 4 * lg, d);
+      for (int j = 0; j < ND; ++j) kv[j] = load4<VK>(kr, 16 * j + 4 * lg, d);
+    } else {
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        kv[0] = load4<VK>(kr, 16 * j + 4 * lg, d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = mfma4(kv[0][e], qv[j][e], s);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     // values past the last key enter as zeros (the cache there may hold anything)
     const int key = k0 + 4 * lg;
 #pragma unroll
     for (int j = 0; j < ND; ++j) {
-      const float *vr = vb + (size_t)min(16 * j + lr, d - 1) * cap;
+      int row = min(16 * j + lr, d - 1);
+      if constexpr (!kAhead) asm volatile("" : "+v"(row));  // no addresses kept over the loop either
+      const float *vr = vb + (size_t)row * cap;
       if constexpr (VV) {
         vv[j] = *(const floatx4 *)(vr + min(key, cap - 4));
 #pragma unroll
@@ -248,11 +264,12 @@ __global__ __launch_bounds__(64 * kAttnWaves) void f32_attention_kernel(
         vv[j] = load4<false>(vr, key, n_keys);
       }
     }
-    floatx4 s = floatx4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (kAhead) {
 #pragma unroll
-    for (int j = 0; j < ND; ++j)
+      for (int j = 0; j < ND; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s = mfma4(kv[j][e], qv[j][e], s);
+        for (int e = 0; e < 4; ++e) s = mfma4(kv[j][e], qv[j][e], s);
+    }
     float bm = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {

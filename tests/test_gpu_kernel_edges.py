@@ -61,6 +61,8 @@ def test_bf16_split_tiles(shape, T, plans):
     (40, 2, 2, 20, 36, 37, 5, 9, "chain:1"),           # one node and its chain
     (128, 1, 1, 128, 64, 16, 300, 431, "total:128"),   # the widest head, eight token tiles
     (60, 2, 1, 30, 44, 50, 0, 8, "total:7"),           # no prefix; head rows unaligned, matrix rows aligned
+    (132, 2, 1, 126, 70, 60, 150, 255, "total:20"),     # wide heads without 16-byte rows, capacity odd
+    (132, 2, 1, 102, 70, 60, 150, 256, "total:33"),     # and values with them
 ])
 def test_f32_sizes(hidden, heads, kv, d, ffn, vocab, L, cap, spec):
     _check(_case("f32", hidden, heads, kv, d, ffn, vocab, L, cap), spec)
