@@ -117,6 +117,16 @@ def _ptr(t) -> int:
 _torch = None
 
 
+def _forget_torch():
+    global _torch
+    _torch = None
+
+
+# a forked child goes through torch.cuda.init() again, which refuses a child of
+# a process that uses the GPU (the raw getters would hand out its stream)
+os.register_at_fork(after_in_child=_forget_torch)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         global _torch

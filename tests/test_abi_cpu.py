@@ -200,6 +200,17 @@ def test_host_template_forms(v):
     assert got.shape == want.shape and np.array_equal(got, want)
 
 
+def test_a_forked_child_initialises_again(monkeypatch):
+    """The cached handle of an initialised torch does not survive a fork, so that
+    torch's own check of forked children is reached."""
+    monkeypatch.setattr(ppd, "_torch", object())
+    pid = os.fork()
+    if pid == 0:
+        os._exit(0 if ppd._torch is None else 1)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+    assert ppd._torch is not None
+
+
 @pytest.mark.parametrize("depth_max,k_max,n_cand,n_prompt,n_ept,seed", [
     (3, 16, 15, 3, 1, 0), (3, 16, 31, 3, 1, 1), (3, 16, 0, 3, 1, 2), (2, 3, 12, 2, 1, 3),
     (4, 5, 20, 3, 1, 4), (3, 16, 7, 3, 2, 5), (1, 16, 16, 3, 1, 6), (3, 16, 24, 3, 1, 7),
