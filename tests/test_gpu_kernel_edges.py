@@ -86,6 +86,38 @@ def test_f32_overflowed_node_stays_invisible():
     assert not np.isfinite(got[last]).all()
 
 
+@pytest.mark.parametrize("hidden,heads,kv,d,L", [
+    (256, 4, 4, 64, 37),   # keys 37 .. 61: three blocks, prefix and tree keys mixed
+    (66, 3, 1, 22, 37),    # heads that are no multiple of 16, no 16-byte rows
+    (132, 2, 1, 126, 44),
+])
+def test_f32_overflowed_node_among_visible_keys(hidden, heads, kv, d, L):
+    """The same for leaves whose keys share their 16-key block with keys that the
+    other nodes see: the block's sums are then formed key by key, which changes
+    their order only (float32 tolerance)."""
+    case = _case("f32", hidden, heads, kv, d, 77, 1000, L)
+    tree = tree_for(case, spec="total:25")
+    ws = workspace(case, tree.T)
+    clean = gpu_step(case, tree, ws)["logits"]
+    leaves = [i for i in range(tree.T) if i not in tree.parent]
+    ids = tree.ids.copy()
+    case.W["tok_emb"][999].fill_(float("inf"))
+    torch.cuda.synchronize()
+    tried = 0
+    for leaf in leaves[:-1]:
+        block = [k for k in range((L + leaf) // 16 * 16, (L + leaf) // 16 * 16 + 16) if k < L + tree.T]
+        if len(block) < 4:
+            continue
+        tried += 1
+        tree.ids[:] = ids
+        tree.ids[leaf] = 999
+        got = gpu_step(case, tree, ws)["logits"]
+        rest = np.delete(np.arange(tree.T), leaf)
+        check_logits(got[rest], clean[rest], "f32", f"leaf {leaf}")
+        assert not np.isfinite(got[leaf]).all()
+    assert tried >= 3
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("f32", 22)])
 @pytest.mark.parametrize("n", [0, 1, 2, 3, 7, 8, 9, 40])  # up to eight rows in registers, more through LDS
 def test_compaction_lengths(dtype, d, n):
