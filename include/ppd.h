@@ -33,8 +33,9 @@
  *   caller and must stay valid until the enqueued work completes.  The
  *   library allocates nothing and keeps no state besides the thread-local
  *   error string and the optional thread-local kernel timer.  Weights and
- *   caches of PPD_BF16 models are bfloat16 (raw 16-bit words), their
- *   activations fp32; PPD_F32 models use float32 throughout.
+ *   caches of PPD_BF16 models are bfloat16 (raw 16-bit words), their residual
+ *   stream and sums float32, the activations a product reads pairs of bfloat16
+ *   (about 16 significant bits); PPD_F32 models use float32 throughout.
  * Streams.  Device calls enqueue on `stream` (a hipStream_t; NULL = default
  *   stream) and return without waiting.  verify -> accept -> compact must be
  *   enqueued in that order on one stream; no host synchronisation is needed
@@ -177,10 +178,9 @@ typedef struct {
  * nodes and caches of up to max_len positions.  0 on invalid input. */
 size_t ppd_workspace_bytes(const ppd_model *model, int32_t t_max, int32_t max_len);
 
-/* Zero the workspace's header -- the status word and a line of zeros the
- * kernels read in place of padding (enqueued on `stream`).  Call once after
- * allocating a workspace; later calls never write the header except for
- * status bits. */
+/* Zero the workspace's header, its first 256 bytes, which hold the status word
+ * (enqueued on `stream`).  Call once after allocating a workspace; later calls
+ * never write the header except for status bits. */
 ppd_status ppd_workspace_init(void *ws, size_t ws_bytes, void *stream);
 
 /*

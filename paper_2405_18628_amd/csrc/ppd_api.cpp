@@ -386,7 +386,6 @@ WsLayout layout_of(const ppd_model *m, int T) {
   w.q = take(sizeof(float) * Tp * nh * d);
   w.attn_o = take(sizeof(float) * Tp * nh * d);
   w.act = take(sizeof(float) * Tp * F);
-  w.max_part_floats = part / sizeof(float);
   w.gemm_part = take(part);
   w.amax = take(sizeof(float2) * w.max_amax_tiles * Tp);
   w.rope = take(sizeof(float2) * Tp * (d / 2));
@@ -683,7 +682,7 @@ size_t ppd_workspace_bytes(const ppd_model *model, int32_t t_max, int32_t max_le
 }
 
 ppd_status ppd_workspace_init(void *ws, size_t ws_bytes, void *stream) {
-  const size_t need = align_up(16);  // status word and the line of zeros
+  const size_t need = align_up(16);  // the header: the status word
   if (!ws || ws_bytes < need) return fail(PPD_EWORKSPACE, "workspace needs at least %zu bytes", need);
   PPD_TRY_HIP(launch_ws_init(ws, need / 4, (hipStream_t)stream));
   return PPD_OK;

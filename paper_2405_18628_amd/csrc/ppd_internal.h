@@ -120,21 +120,11 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, PPD_WAVE));
-  return v;
-}
-
 // ---------------------------------------------------------------------------
 // workspace layout (computed on the host, passed to kernels as pointers)
 
-// the first 256 bytes of the workspace hold the status word (offset 0) and a
-// 64-byte line of zeros (offset PPD_WS_ZEROS) that is never written
-#define PPD_WS_ZEROS 64
-
 struct WsLayout {
-  size_t status;      // uint32 [4]
+  size_t status;      // uint32 [4], the workspace's header (256 bytes)
   size_t x;           // float  [T_pad][H]        residual stream
   size_t xg;          // x * gain of the next norm: operand planes [T_pad][H] (bf16 models)
   size_t ss;          // float  [max_ss][T_pad]   sum-of-squares partials
@@ -142,14 +132,13 @@ struct WsLayout {
   size_t attn_o;      // operand planes [T_pad][nh d] attention output (fp32 path: float)
   size_t act;         // operand planes [T_pad][F] SwiGLU output (fp32 path: float)
   size_t attn_part;   // float  [nh][max_splits][T_pad][PPD_ATTN_OROW]; the same memory as xg
-  size_t gemm_part;   // float  [max_part_floats]
+  size_t gemm_part;   // partial sums of split GEMMs
   size_t amax;        // float2 [max_amax_tiles][T_pad]
   size_t rope;        // float2 [T_pad][d/2]      (cos, sin)
   size_t ctr;         // uint32 [n_ctr]           tile / head counters (zeroed per step)
   size_t n_ctr;
   size_t total;
   int max_ss, max_splits, max_amax_tiles;
-  size_t max_part_floats;
 };
 
 #define PPD_ATTN_MAX_SPLITS 64

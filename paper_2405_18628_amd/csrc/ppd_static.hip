@@ -50,7 +50,7 @@ extern "C" ppd_status ppd_verify_step_static(const ppd_model *model, const ppd_k
     return ppd_fail(PPD_EWORKSPACE,
                     "the step needs %zu bytes of workspace, more than the static %zu-byte array",
                     need, (size_t)PPD_STATIC_WS_BYTES);
-  // the header (status word, line of zeros) starts at zero for every call:
+  // the header (status word) starts at zero for every call:
   // the array keeps whatever the previous call on this GPU left
   ppd_status st = ppd_workspace_init(ws, need, stream);
   if (st != PPD_OK) return st;
