@@ -43,10 +43,11 @@ __device__ __forceinline__ floatx4 load4(const float *row, int k, int n) {
 // tokens); its four waves deal the columns, 16 at a time: lane l loads columns
 // k + 4 (l / 16) .. + 3 of row l % 16 (weights, the A operand) and of token
 // l % 16 (the B operand), and instruction e multiplies element e of both, so
-// the 16 columns take four instructions.  Every launch here is bound by a few
-// memory round trips; the 16 x 16 tiles give the chip as many workgroups as
-// the matrix has tiles, and the waves' split of the columns shortens each
-// one's chain.  The waves' sums meet in LDS; wave 0 finishes the tile.
+// the 16 columns take four instructions.  Every launch here is bound by memory
+// round trips, one for each 64 columns (the loop is not unrolled: 4 at 256
+// columns, 11 at 688); the 16 x 16 tiles give the chip as many workgroups as
+// the matrix has tiles, and the waves' split of the columns shortens each one's
+// chain.  The waves' sums meet in LDS; wave 0 finishes the tile.
 template <int KIND, bool VEC>
 __global__ __launch_bounds__(256) void f32_gemm_kernel(F32Gemm g) {
   constexpr bool kNorm = KIND != GEMM_RESID;
@@ -76,7 +77,6 @@ __global__ __launch_bounds__(256) void f32_gemm_kernel(F32Gemm g) {
 #pragma unroll
   for (int q = 0; q < S; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
   float ss = 0.f;
-#pragma unroll 4
   for (int k0 = 16 * wave; k0 < K; k0 += 64) {
     const int k = k0 + 4 * lg;
     floatx4 b = load4<VEC>(a, k, K);
