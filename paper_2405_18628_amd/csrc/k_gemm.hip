@@ -39,7 +39,7 @@
 //    within a set, to TX tiles x s K-slices.  s = 1 needs no exchange between
 //    workgroups; s > 1 trades one (partial sums through the XCD's L2 behind a
 //    counter, a bounded wait) for 1 / s of the activation bytes per workgroup
-//    (plan_gemm chooses);
+//    (plan_gemm chooses; two_slice_gw: tiles with a cheaper exchange);
 //  * epilogues: RMSNorm row scale, RoPE + query / key / value stores into the
 //    cache (QKV), residual add, the next norm's operand planes and sums of
 //    squares (output / down projections), SwiGLU into operand planes
@@ -47,11 +47,11 @@
 //
 // Measured (us a launch; in brackets with fp32 activations, split, staged
 // through LDS and behind a barrier per chunk in every workgroup, as this
-// kernel did before): 7B, T = 1: QKV 21.2 (25.6), output 11.8 and down
-// projection 24.3 (18.2 on average), gate/up 33.2 (37.6); T = 64: QKV 31.1
-// (31.3), output 16.9 (18.5), down 30.3 (32.0), gate/up 41.6 (43.7), LM head
-// 57.9 (62.7); 13B, T = 128: QKV 60 (77), gate/up 91 (123), LM head 120
-// (134).  What bounds it: up to T = 32 the HBM stream (5.4 TB/s over a gate/up
+// kernel did before): 7B, T = 1: QKV 20.0 (25.6), output 11.1 and down
+// projection 21.2 (18.2 on average), gate/up 31.6 (37.6); T = 64: QKV 31.1
+// (31.3), output 16.7 (18.5), down 30.4 (32.0), gate/up 41.3 (43.7), LM head
+// 57.0 (62.7); 13B, T = 128: QKV 60 (77), gate/up 89 (123), LM head 119
+// (134).  What bounds it: up to T = 32 the HBM stream (5.7 TB/s over a gate/up
 // launch at T = 1), beyond that the compute unit's load path, which the
 // activations share.
 #include <algorithm>
